@@ -271,55 +271,193 @@ __global__ void __launch_bounds__(kBlock)
   if (threadIdx.x == 0) red[(long long)b * gridDim.x + blockIdx.x] = t;
 }
 
-__global__ void spectrum_abs_kernel(const double* __restrict__ series, long long n, double dt,
-                                    const double* __restrict__ omega, int n_omega, double* __restrict__ out) {
-  const int w = blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= n_omega) return;
-  const double om = omega[w];
-  double acc = 0.0;
-  for (long long s = 0; s < n; ++s) {
-    const double c = (s == 0 || s == n - 1) ? 0.5 : 1.0;
-    double sn, cs;
-    sincos(om * (double)s * dt, &sn, &cs);
-    // Im(e^{i w t} R) = sin(wt) Re R + cos(wt) Im R
-    acc += c * (sn * series[2 * s] + cs * series[2 * s + 1]);
-  }
-  out[w] = om * acc * dt;
+// ---------------------------------------------------------------------------
+// Spectral sums of Sec. III.  The phase factors exp(i omega s dt) of
+// consecutive samples differ by one rotation, so a thread evaluates sincos
+// once per kPhaseChunk * kPhaseRestart samples of its omega and rotates in
+// between (four operations a sample; one sincos takes about a hundred).  Two
+// levels keep the rotations' rounding small: a chunk's samples are rotated
+// from the chunk's first factor, the chunks' first factors from the last
+// sincos, so no factor is more than kPhaseChunk + kPhaseRestart rotations away
+// from a sincos (2e-15; the product omega * s * dt itself rounds at 1e-16 of
+// a phase that reaches several hundred).
+// ---------------------------------------------------------------------------
+constexpr int kPhaseChunk = 16;
+constexpr int kPhaseRestart = 8;
+constexpr int kSpectrumThreads = 1024;
+
+struct Phase {
+  double re, im;
+};
+__device__ __forceinline__ Phase phase_of(double x) {
+  Phase p;
+  sincos(x, &p.im, &p.re);
+  return p;
+}
+__device__ __forceinline__ Phase rotate(Phase a, Phase b) {
+  return {fma(a.re, b.re, -(a.im * b.im)), fma(a.re, b.im, a.im * b.re)};
 }
 
-// A[t1][w3] = sum_t3 c dt3 e^{i w3 t3} R3[t1][t3]
-__global__ void spectrum_corr_t3_kernel(const double* __restrict__ r3, int n1, int n3, double dt3,
-                                        const double* __restrict__ w3, int nw3, double* __restrict__ work) {
-  const int w = blockIdx.x * blockDim.x + threadIdx.x;
-  const int i1 = blockIdx.y;
-  if (w >= nw3 || i1 >= n1) return;
-  const double om = w3[w];
-  const double* r = r3 + (long long)i1 * n3 * 2;
-  double re = 0.0, im = 0.0;
-  for (int s = 0; s < n3; ++s) {
-    const double c = (s == 0 || s == n3 - 1) ? 0.5 : 1.0;
-    double sn, cs;
-    sincos(om * (double)s * dt3, &sn, &cs);
-    re += c * (cs * r[2 * s] - sn * r[2 * s + 1]);
-    im += c * (sn * r[2 * s] + cs * r[2 * s + 1]);
+// one complex sample (aligned as a double: callers' series need not be
+// aligned to 16 bytes)
+struct Sample {
+  double re, im;
+};
+
+// sum_{s = s0}^{s1 - 1} c_s Im(e^{i om s dt} x_r[s]) for R complex rows x_r of
+// n samples (row stride in samples), added to acc; c_s the trapezoid weights
+template <int R>
+__device__ __forceinline__ void phase_sums(const Sample* __restrict__ x, long long row_stride, long long n,
+                                           long long s0, long long s1, double om, double dt, double (&acc)[R]) {
+  const Phase e1 = phase_of(om * dt), ec = phase_of(om * (double)kPhaseChunk * dt);
+  Phase base = {1.0, 0.0};
+  int k = 0;
+  for (long long c = s0; c < s1; c += kPhaseChunk, ++k) {
+    base = (k % kPhaseRestart == 0) ? phase_of(om * (double)c * dt) : rotate(base, ec);
+    Phase e = base;
+    if (c > 0 && c + kPhaseChunk <= s1 && c + kPhaseChunk < n) {
+#pragma unroll
+      for (int j = 0; j < kPhaseChunk; ++j) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const Sample v = x[r * row_stride + c + j];
+          acc[r] = fma(e.im, v.re, fma(e.re, v.im, acc[r]));
+        }
+        if (j + 1 < kPhaseChunk) e = rotate(e, e1);
+      }
+    } else {
+      // a chunk with an end of the series, or a partial one
+      for (long long s = c; s < min(s1, c + kPhaseChunk); ++s) {
+        const double g = (s == 0 || s == n - 1) ? 0.5 : 1.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const Sample v = x[r * row_stride + s];
+          acc[r] = fma(g * e.im, v.re, fma(g * e.re, v.im, acc[r]));
+        }
+        e = rotate(e, e1);
+      }
+    }
   }
-  work[((long long)i1 * nw3 + w) * 2] = re * dt3;
-  work[((long long)i1 * nw3 + w) * 2 + 1] = im * dt3;
 }
 
-// out[w3][w1] = sum_t1 c dt1 2 cos(w1 t1) Im A[t1][w3]
-__global__ void spectrum_corr_t1_kernel(const double* __restrict__ work, int n1, double dt1,
-                                        const double* __restrict__ w1, int nw1, int nw3, double* __restrict__ out) {
-  const int a = blockIdx.x * blockDim.x + threadIdx.x;
-  const int w = blockIdx.y;
-  if (a >= nw1 || w >= nw3) return;
-  const double om = w1[a];
-  double acc = 0.0;
-  for (int s = 0; s < n1; ++s) {
-    const double c = (s == 0 || s == n1 - 1) ? 0.5 : 1.0;
-    acc += c * 2.0 * cos(om * (double)s * dt1) * work[((long long)s * nw3 + w) * 2 + 1];
+// samples per segment when n samples are split into at most `segs` segments
+// of whole chunks
+__host__ __device__ __forceinline__ long long segment_length(long long n, int segs) {
+  const long long l = (n + segs - 1) / segs;
+  return (l + kPhaseChunk - 1) / kPhaseChunk * kPhaseChunk;
+}
+
+// out[w] = omega_w dt sum_s c_s Im(e^{i omega_w s dt} R[s]).  Bound by FP64
+// issue and by how many CUs take part: a workgroup owns `wpb` frequencies and
+// splits the samples over blockDim / wpb segments, whose sums meet in LDS
+// (no scratch memory, fixed order).  20001 samples at 2001 frequencies take
+// 23 us a call; one thread per frequency over all samples with a sincos per
+// sample took 4430 us.
+__global__ void __launch_bounds__(kSpectrumThreads)
+    spectrum_abs_kernel(const Sample* __restrict__ series, long long n, double dt, const double* __restrict__ omega,
+                        int n_omega, int wpb, double* __restrict__ out) {
+  __shared__ double sh[kSpectrumThreads];
+  const int tid = threadIdx.x, segs = blockDim.x / wpb;
+  const int seg = tid / wpb, w = blockIdx.x * wpb + tid % wpb;
+  const double om = omega[min(w, n_omega - 1)];
+  const long long len = segment_length(n, segs);
+  const long long s0 = seg * len, s1 = min(n, s0 + len);
+  double acc[1] = {0.0};
+  if (s0 < s1) phase_sums<1>(series, 0, n, s0, s1, om, dt, acc);
+  sh[tid] = acc[0];
+  for (int half = segs / 2; half > 0; half /= 2) {
+    __syncthreads();
+    if (seg < half) sh[tid] += sh[tid + half * wpb];
   }
-  out[(long long)w * nw1 + a] = acc * dt1;
+  if (seg == 0 && w < n_omega) out[w] = om * sh[tid] * dt;
+}
+
+// im[t1][w3] = Im sum_t3 c dt3 e^{i w3 t3} R3[t1][t3], the part of the t3 sums
+// that the spectrum needs.  A lane holds one frequency and R coherence times,
+// so the phase factors are shared by R rows and the samples are the same for
+// the whole wave (scalar loads); the sixteen waves of a workgroup take a
+// sixteenth of the samples each and meet in LDS.  The launcher takes the
+// largest R that still gives about one workgroup per CU.  64 x 4001 samples
+// at 401 frequencies take 37 us (bound by the latency of the scalar loads:
+// FP64 issue alone is 12 us); with one thread per (t1, frequency) and a
+// sincos per sample the two passes took 1180 us.
+constexpr int kCorrWaves = kSpectrumThreads / 64;
+template <int R>
+__global__ void __launch_bounds__(kSpectrumThreads)
+    spectrum_corr_t3_kernel(const Sample* __restrict__ r3, int n1, int n3, double dt3,
+                            const double* __restrict__ w3, int nw3, double* __restrict__ im) {
+  __shared__ double sh[kCorrWaves][R][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int seg = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: the samples come through scalar loads
+  const int i0 = blockIdx.y * R;
+  const double om = w3[min((int)blockIdx.x * 64 + lane, nw3 - 1)];
+  const long long len = segment_length(n3, kCorrWaves);
+  const long long s0 = seg * len, s1 = min((long long)n3, s0 + len);
+  double acc[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[r] = 0.0;
+  // (the last workgroup's rows may run past n1: it takes its rows from the end)
+  const int row = min(i0, max(n1 - R, 0));
+  if (s0 < s1) phase_sums<R>(r3 + (long long)row * n3, n3, n3, s0, s1, om, dt3, acc);
+#pragma unroll
+  for (int r = 0; r < R; ++r) sh[seg][r][lane] = acc[r];
+  __syncthreads();
+  for (int e = tid; e < R * 64; e += kSpectrumThreads) {
+    const int r = e / 64, w = blockIdx.x * 64 + e % 64;
+    double s = 0.0;
+    for (int k = 0; k < kCorrWaves; ++k) s += sh[k][r][e % 64];
+    if (w < nw3) im[(long long)(row + r) * nw3 + w] = s * dt3;
+  }
+}
+
+// out[w3][w1] = sum_t1 c dt1 2 cos(w1 t1) Im A[t1][w3]: a lane holds one w1 and
+// kCorrRows frequencies w3, which share the cosine; the waves of a workgroup
+// take every kCorrT1Waves-th chunk of kCorrT1Chunk coherence times (whose
+// sums, the same for the whole wave, come through scalar loads issued
+// together) and meet in LDS.  6.9 us for 64 coherence times at 401 x 401
+// frequencies; 21 us as one wave per workgroup with loads one by one.
+constexpr int kCorrRows = 4;
+constexpr int kCorrT1Waves = 8;
+constexpr int kCorrT1Chunk = 8;
+__global__ void __launch_bounds__(64 * kCorrT1Waves)
+    spectrum_corr_t1_kernel(const double* __restrict__ im, int n1, double dt1, const double* __restrict__ w1,
+                            int nw1, int nw3, double* __restrict__ out) {
+  __shared__ double sh[kCorrT1Waves][kCorrRows][64];
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w0 = blockIdx.y * kCorrRows;
+  const double om = w1[min((int)blockIdx.x * 64 + lane, nw1 - 1)];
+  const Phase e1 = phase_of(om * dt1);
+  double acc[kCorrRows] = {};
+  for (int c = wid * kCorrT1Chunk; c < n1; c += kCorrT1Waves * kCorrT1Chunk) {
+    double x[kCorrT1Chunk][kCorrRows];
+#pragma unroll
+    for (int j = 0; j < kCorrT1Chunk; ++j)
+#pragma unroll
+      for (int r = 0; r < kCorrRows; ++r)
+        x[j][r] = im[(long long)min(c + j, n1 - 1) * nw3 + min(w0 + r, nw3 - 1)];
+    Phase e = phase_of(om * (double)c * dt1);
+#pragma unroll
+    for (int j = 0; j < kCorrT1Chunk; ++j) {
+      const int s = c + j;
+      if (s < n1) {
+        const double g = (s == 0 || s == n1 - 1) ? e.re : 2.0 * e.re;
+#pragma unroll
+        for (int r = 0; r < kCorrRows; ++r) acc[r] = fma(g, x[j][r], acc[r]);
+      }
+      e = rotate(e, e1);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kCorrRows; ++r) sh[wid][r][lane] = acc[r];
+  __syncthreads();
+  // wave r sums frequency row r
+  const int r = wid, a = blockIdx.x * 64 + lane;
+  if (r >= kCorrRows || w0 + r >= nw3 || a >= nw1) return;
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < kCorrT1Waves; ++k) s += sh[k][r][lane];
+  out[(long long)(w0 + r) * nw1 + a] = s * dt1;
 }
 
 __global__ void clear_flag_kernel(int* flag) {
@@ -475,19 +613,35 @@ hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStrea
 
 hipError_t launch_spectrum_abs(const double* series, long long n, double dt, const double* omega, int n_omega,
                                double* out, hipStream_t s) {
-  hipLaunchKernelGGL(spectrum_abs_kernel, dim3((n_omega + 127) / 128), dim3(128), 0, s, series, n, dt, omega,
-                     n_omega, out);
+  // frequencies per workgroup: about one workgroup per CU, 4 to 64 (a
+  // frequency's samples then split over up to 256 segments); segments: a
+  // power of two, at least two chunks of samples each
+  int wpb = 4;
+  while (wpb < 64 && n_omega > 256 * wpb) wpb *= 2;
+  int segs = 64 / wpb > 1 ? 64 / wpb : 1;
+  while (segs * wpb * 2 <= kSpectrumThreads && n >= (long long)segs * 4 * kPhaseChunk) segs *= 2;
+  hipLaunchKernelGGL(spectrum_abs_kernel, dim3((n_omega + wpb - 1) / wpb), dim3(wpb * segs), 0, s,
+                     reinterpret_cast<const Sample*>(series), n, dt, omega, n_omega, wpb, out);
   return hipGetLastError();
 }
 
 hipError_t launch_spectrum_corr(const double* r3, int n1, int n3, double dt1, double dt3, const double* w1,
                                 int nw1, const double* w3, int nw3, double* work, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(spectrum_corr_t3_kernel, dim3((nw3 + 127) / 128, n1), dim3(128), 0, s, r3, n1, n3, dt3, w3,
-                     nw3, work);
+  // coherence times per lane: the most that still give about one workgroup
+  // per CU (with 64 x 401: 2 rows, 224 workgroups); at most n1 rows
+  const unsigned bx = (unsigned)((nw3 + 63) / 64);
+  int rows = 8;
+  while (rows > 1 && (rows > n1 || (long long)bx * ((n1 + rows - 1) / rows) < 200)) rows /= 2;
+  const dim3 grid(bx, (unsigned)((n1 + rows - 1) / rows)), block(kSpectrumThreads);
+  const Sample* x = reinterpret_cast<const Sample*>(r3);
+#define F(R) hipLaunchKernelGGL((spectrum_corr_t3_kernel<R>), grid, block, 0, s, x, n1, n3, dt3, w3, nw3, work)
+  if (rows == 8) { F(8); } else if (rows == 4) { F(4); } else if (rows == 2) { F(2); } else { F(1); }
+#undef F
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(spectrum_corr_t1_kernel, dim3((nw1 + 127) / 128, nw3), dim3(128), 0, s, work, n1, dt1, w1,
-                     nw1, nw3, out);
+  hipLaunchKernelGGL(spectrum_corr_t1_kernel, dim3((nw1 + 63) / 64, (nw3 + kCorrRows - 1) / kCorrRows),
+                     dim3(64 * kCorrT1Waves), 0, s,
+                     work, n1, dt1, w1, nw1, nw3, out);
   return hipGetLastError();
 }
 

@@ -1,0 +1,62 @@
+"""The spectral sums at the edges of their splits (samples over segments of
+whole chunks, frequencies over workgroups, coherence times over lanes'
+rows) against the same trapezoid sums in NumPy.
+
+Tolerance: both sides round the phase omega s dt (up to three roundings of
+half an ulp each side) and the kernels rotate each factor from its last sincos
+by at most 24 products of two roundings; every factor is then within
+eps (4 phase + 64) of the other side's, and so is each term relative to its
+sample."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+if not torch.cuda.is_available():  # pragma: no cover - CPU container
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_1706_09590_amd import qhfpe  # noqa: E402
+
+EPS = np.finfo(np.float64).eps
+
+
+def weights(n):
+    c = np.ones(n)
+    c[0] = c[-1] = 0.5
+    return c
+
+
+@pytest.mark.parametrize("n,n_omega", [(2, 1), (15, 3), (16, 5), (17, 64), (33, 65), (64, 1025), (129, 2049),
+                                       (2049, 257), (4097, 20000)])
+def test_absorption_sums(n, n_omega):
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal(n) + 1j * rng.standard_normal(n)
+    dt, om = 0.01, np.linspace(-3.0, 25.0, n_omega)
+    buf = torch.zeros(2 * n + 1, dtype=torch.float64, device="cuda")
+    buf[1:] = torch.from_numpy(x.view(np.float64)).cuda()  # a series on an 8-byte boundary
+    omd = torch.from_numpy(om).cuda()
+    got = torch.empty(n_omega, dtype=torch.float64, device="cuda")
+    s = torch.cuda.current_stream()
+    rc = qhfpe.lib().qhfpe_spectrum_abs(buf[1:].data_ptr(), n, dt, omd.data_ptr(), n_omega, got.data_ptr(),
+                                        s.cuda_stream)
+    assert rc == qhfpe.OK
+    ph = om[:, None] * np.arange(n) * dt
+    ref = om * dt * ((np.sin(ph) * x.real + np.cos(ph) * x.imag) @ weights(n))
+    tol = np.abs(om) * dt * np.abs(x).sum() * EPS * (4 * np.abs(om) * n * dt + 64)
+    assert np.all(np.abs(got.cpu().numpy() - ref) <= tol + 1e-300)
+
+
+@pytest.mark.parametrize("n1,n3,nw1,nw3", [(2, 2, 1, 1), (3, 17, 5, 3), (9, 200, 64, 64), (17, 257, 65, 130),
+                                           (33, 300, 401, 401), (64, 1001, 70, 2000), (7, 4001, 3, 9)])
+def test_correlation_sums(n1, n3, nw1, nw3):
+    rng = np.random.default_rng(n1 * n3)
+    x = rng.standard_normal((n1, n3)) + 1j * rng.standard_normal((n1, n3))
+    d1, d3 = 0.05, 0.01
+    w1, w3 = np.linspace(-2.0, 20.0, nw1), np.linspace(0.0, 22.0, nw3)
+    got = qhfpe.spectrum_corr(x, d1, d3, w1, w3).cpu().numpy()
+    ph = w3[:, None] * np.arange(n3) * d3
+    A = d3 * ((np.sin(ph) * weights(n3)) @ x.real.T + (np.cos(ph) * weights(n3)) @ x.imag.T)
+    ref = 2.0 * d1 * (A * weights(n1)) @ np.cos(w1[:, None] * np.arange(n1) * d1).T
+    scale = 2.0 * d1 * d3 * np.abs(x).sum()
+    assert np.max(np.abs(got - ref)) <= scale * EPS * (4 * (22.0 * n3 * d3 + 20.0 * n1 * d1) + 2 * 64)
