@@ -108,6 +108,12 @@ Layout make_layout(const qhfpe_params* p) {
   const long long cells = (long long)(p->depth + 1) * p->nq * p->np;
   const long long pack_blocks = (cells + kBlock - 1) / kBlock;
   L.red_count = (size_t)p->batch * (size_t)std::max<long long>(2 * pack_blocks, 1024);
+  // the partial sums of qhfpe_closure_stats, where the scratch states of a
+  // small handle could not hold them
+  if (wave_supported(p->n_states, p->np)) {
+    const size_t need = closure_stats_scratch_bytes();
+    if (2 * L.state_bytes < need) L.red_count = std::max(L.red_count, (need + sizeof(double) - 1) / sizeof(double));
+  }
   size_t off = 0;
   L.off_y = off;
   off += L.state_bytes;
@@ -1273,8 +1279,17 @@ int qhfpe_closure_stats(qhfpe_t* h, int32_t level, double* d_stats) {
   for (int b = 0; b < h->p.batch; ++b)
     if (h->mdepth[b] <= level)
       return fail(QHFPE_EUNSUPPORTED, "member %d (depth %d) has no level %d", b, h->mdepth[b], level + 1);
+  // partial sums in the scratch states v_a, v_b (free between steps), or in the
+  // reduction buffer where that is larger
+  size_t bytes = 2 * h->L.state_bytes;
+  double* scratch = static_cast<double*>(h->va());
+  if (bytes < h->L.red_count * sizeof(double)) {
+    bytes = h->L.red_count * sizeof(double);
+    scratch = h->red();
+  }
   HIP_TRY(launch_closure_stats(h->p.precision, h->p.np, h->y(), level, h->L.member_elems, h->L.level_elems,
-                               h->L.comp_elems, h->p.nq, h->p.batch, h->p.p_min, h->dp, d_stats, h->stream));
+                               h->L.comp_elems, h->p.nq, h->p.batch, h->p.p_min, h->dp, scratch, bytes, d_stats,
+                               h->stream));
   return QHFPE_OK;
 }
 
@@ -1346,12 +1361,15 @@ int qhfpe_closure_train(const double* d_stats, const float* d_prior, double ridg
             init[TL::w3 + ((tq * 5 + tp) * H + c) * kClosureOut + o] =
                 k0[(((tq + kClosureHalf - 2) * S + (tp + kClosureHalf - 2)) * kClosureIn + c) * kClosureOut + o];
   }
+  // the layers alternate between two buffers and end in the first
+  int from = iters % 2 ? TL::g1 : TL::w1, to = iters % 2 ? TL::w1 : TL::g1;
+  if (from != TL::w1) std::copy_n(init.begin() + TL::w1, TL::nparam, init.begin() + from);
   HIP_TRY(hipMemcpyAsync(d_state, init.data(), init.size() * sizeof(float), hipMemcpyHostToDevice, s));
-  for (int t = 1; t <= iters; ++t) {
+  for (int t = 1; t <= iters; ++t, std::swap(from, to)) {
     // learning rate decays geometrically from lr to lr_final
     const double f = iters > 1 ? (double)(t - 1) / (iters - 1) : 0.0;
     const float lr_t = (float)(lr * std::pow(lr_final / lr, f));
-    HIP_TRY(launch_closure_train_step(d_stats, d_prior, ridge, d_state, t, lr_t, nullptr, s));
+    HIP_TRY(launch_closure_train_step(d_stats, d_prior, ridge, d_state, from, to, t, lr_t, s));
   }
   // the composite kernel of the final layers and its normalised loss
   double* d_loss = reinterpret_cast<double*>(d_state + TL::loss);

@@ -147,7 +147,8 @@ constexpr int kClosureStatsA = 25 * 25 * kClosureIn * kClosureIn;         // A[2
 constexpr int kClosureStatsC = 13 * 13 * kClosureIn * kClosureOut;        // C[13][13][8][4]
 constexpr int kClosureStatsSize = kClosureStatsA + kClosureStatsC + 1;    // + yy
 constexpr int kClosureWeightElems = 16 * 7 * 16 * 16;                     // BF16 MFMA B layout
-// Training state (floats): the three layers, their gradients, Adam moments,
+// Training state (floats): the three layers, the layers after the running
+// iteration (the two buffers swap from iteration to iteration), Adam moments,
 // the 9x9 product of the first two layers and its gradient, the composite
 // kernel and its gradient, and per-entry loss terms (doubles).
 struct ClosureTrainLayout {
@@ -171,11 +172,14 @@ hipError_t launch_closure_weights(const float* K, unsigned short* wb, hipStream_
 hipError_t launch_closure_apply(int precision, int np, const void* v, int level, long long member_stride,
                                 long long level_stride, long long comp_stride, int nq, int batch, double p0,
                                 double dp, const unsigned short* wb, void* out, long long out_stride, hipStream_t s);
+// scratch: at least closure_stats_scratch_bytes() of device memory for the
+// partial sums; more lets more workgroups take part
+size_t closure_stats_scratch_bytes();
 hipError_t launch_closure_stats(int precision, int np, const void* v, int level, long long member_stride,
                                 long long level_stride, long long comp_stride, int nq, int batch, double p0,
-                                double dp, double* stats, hipStream_t s);
-hipError_t launch_closure_train_step(const double* stats, const float* prior, double ridge, float* state, int t,
-                                     float lr, double* loss, hipStream_t s);
+                                double dp, double* scratch, size_t scratch_bytes, double* stats, hipStream_t s);
+hipError_t launch_closure_train_step(const double* stats, const float* prior, double ridge, float* state, int from,
+                                     int to, int t, float lr, hipStream_t s);
 hipError_t launch_closure_compose(const double* stats, float* state, double* loss, hipStream_t s);
 hipError_t launch_closure_loss(const double* stats, const float* K, float* g, double* terms, double* loss,
                                hipStream_t s);

@@ -301,3 +301,40 @@ def test_ridge_training_and_the_loss_entry_point():
     Kh, _ = qhfpe.closure_train(stats, iters=400, lr=3e-3, lr_final=1e-4, seed=3, prior=torch.from_numpy(K0).cuda(),
                                 ridge=1e6)
     assert rel(Kh.cpu().numpy(), K0) < 1e-2
+
+
+@pytest.mark.parametrize("np_,nq,batch,precision", [(128, 4, 1, "fp32"), (128, 13, 1, "fp64"), (256, 27, 2, "fp64"),
+                                                    (128, 67, 3, "fp32")])
+def test_statistics_split_over_row_chunks(np_, nq, batch, precision):
+    """Sizes at the edges of the statistics' split: fewer rows than waves (and
+    a state too small to hold the partial sums), ragged chunks, one more than
+    a whole number of chunks, members that share a chunk; unsmoothed data up
+    to the q edges.  FP64 sums of the same products in another order:
+    n_terms * eps * the sum of magnitudes, for every entry."""
+    d = inputs.model_dict(inputs.SMALL_ABSORPTION["model"], nq=nq, np=np_, depth=1)
+    S = np.stack([inputs.random_hierarchy(1, 2, nq, np_, seed=300 + b, smooth=False) for b in range(batch)])
+    P = qhfpe.Propagator(d, batch=batch, precision=precision)
+    try:
+        P.set_state(torch.from_numpy(S))
+        stats = torch.zeros(qhfpe.CLOSURE_STATS_DOUBLES, dtype=torch.float64, device="cuda")
+        P.closure_stats(0, stats)
+        S = P.get_state().cpu().numpy()  # (the rounded state in FP32)
+    finally:
+        P.close()
+    got = stats.cpu().numpy()
+    pk = [np.stack([S[:, n, 0, 0].real, S[:, n, 1, 1].real, S[:, n, 0, 1].real, S[:, n, 0, 1].imag]) for n in (0, 1)]
+    dp = (d["p_max"] - d["p_min"]) / np_
+    X = np.concatenate([pk[0], (d["p_min"] + dp * np.arange(np_)) * pk[0]])
+    Z = np.zeros((8, batch, nq + 24, np_))
+    Z[:, :, 12:12 + nq] = X
+
+    def tap(Z, H, dq, dpo):
+        return np.roll(Z[:, :, dq + 12 - H:dq + 12 - H + nq], H - dpo, -1).reshape(8, -1)
+
+    def sums(Z, X, Y):
+        A = [X.reshape(8, -1) @ tap(Z, 12, i, j).T for i in range(25) for j in range(25)]
+        C = [tap(Z, 6, i, j) @ Y.reshape(4, -1).T for i in range(13) for j in range(13)]
+        return np.concatenate([np.ravel(A), np.ravel(C), [(Y * Y).sum()]])
+
+    ref, mag = sums(Z, X, pk[1]), sums(np.abs(Z), np.abs(X), np.abs(pk[1]))
+    assert np.all(np.abs(got - ref) <= batch * nq * np_ * np.finfo(np.float64).eps * mag + 1e-300)
