@@ -197,15 +197,18 @@ double qhfpe_morse_gauss_potential(int32_t j, int32_t l, double x, void* ctx);
 /* Tile variant of the fused RK stage.  2, 4, 8: each thread of a stage
  * workgroup owns cells_per_thread consecutive q columns (2, 4 or 8 for FP32
  * two-state; 2 or 4 for FP64 two-state and FP32 three-state; 2 for FP64
- * three-state).  1: the wave-independent variant, one 64-lane wave per
- * task of q columns, each lane holding np/64 consecutive p nodes: two
- * states at np = 128 or 256 (512/np columns per task); three states with
- * constant couplings at np = 128 (two columns per task) or 256 (one).  0 = default: 1 where available, else 4 (2 for three states); it
- * is also the variant at create.  With a q-dependent coupling only tile 2
- * and, for two states, tile 1 exist (see qhfpe_set_potential).  Variants compute the same operations per
- * cell; results agree to rounding (the compiled instruction order and the
- * grouping of the trace partial sums differ).  QHFPE_EUNSUPPORTED if the
- * variant does not exist for this precision, state count and np. */
+ * three-state).  1 (np = 128 or 256; three states with constant couplings):
+ * the wave-independent variant, one 64-lane wave per group of q columns of
+ * one level.  0 = default: 1 where available, else 4 (2 for three states); it
+ * is also the variant at create.  At np = 32, 48, 64, 96 and 192 the
+ * wave-independent variant computes the default (constant couplings, and for
+ * two states the q-dependent couplings' tile 2).  With a q-dependent coupling
+ * only tile 2 and, for two states, tile 1 exist (see qhfpe_set_potential).
+ * The columns per wave follow the size of the handle's launches; results do
+ * not depend on them.  Variants compute the same operations per cell; results
+ * agree to rounding (the compiled instruction order and the grouping of the
+ * trace partial sums differ).  QHFPE_EUNSUPPORTED if the variant does not
+ * exist for this precision, state count and np. */
 int qhfpe_set_tile(qhfpe_t* h, int32_t cells_per_thread);
 
 /* Pick the fastest tile variant for this handle by timing reps stage launches

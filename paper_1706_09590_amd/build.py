@@ -18,7 +18,8 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libqhfpe.so")
 
 SOURCES = ["qhfpe_api.cpp", "aux_kernels.hip", "closure.hip", "stage_f64_ns2.hip", "stage_f64_ns3.hip",
-           "stage_f32_ns2.hip", "stage_f32_ns3.hip"]
+           "stage_f32_ns2.hip", "stage_f32_ns3.hip", "wave_f64_ns2.hip", "wave_f64_ns3.hip", "wave_f32_ns2.hip",
+           "wave_f32_ns3.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -202,20 +202,20 @@ __global__ void __launch_bounds__(kBlock)
   for (int c = 0; c < NC; ++c) p[c * g.comp_stride] = T(c == 0 ? w : 0.0);
 }
 
-// Level-0 trace partials with the same tiling as the stage kernel.
+// Level-0 trace partials with the same tiling as the stage kernel: one wave
+// per tile.
 template <typename T, int NS>
 __global__ void __launch_bounds__(kBlock)
     trace_kernel(GridDesc g, const T* __restrict__ packed, DipoleMu mu, int tq, int ntiles,
                  double* __restrict__ partials, int slot) {
-  __shared__ double sh[kBlock / 64];
-  const int tile = blockIdx.x, b = blockIdx.y;
+  const int lane = threadIdx.x & 63;
+  const int tile = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6), b = blockIdx.y;
+  if (tile >= ntiles) return;
   const T* p = packed + (long long)b * g.member_stride;
-  const int cells = tq * g.np;
+  const int cells = min(tq, g.nq - tile * tq) * g.np;
   double tr = 0.0;
-  for (int e = threadIdx.x; e < cells; e += kBlock) {
-    const int q = tile * tq + e / g.np;
-    if (q >= g.nq) continue;
-    const long long ia = (long long)q * g.np + e % g.np;
+  for (int e = lane; e < cells; e += 64) {
+    const long long ia = (long long)tile * tq * g.np + e;
 #pragma unroll
     for (int j = 0; j < NS; ++j) tr += mu.m[j][j] * (double)p[j * g.comp_stride + ia];
 #pragma unroll
@@ -224,19 +224,24 @@ __global__ void __launch_bounds__(kBlock)
       for (int k = j + 1; k < NS; ++k)
         tr += 2.0 * mu.m[j][k] * (double)p[Packing<NS>::re(j, k) * g.comp_stride + ia];
   }
-  const double s = block_sum(tr, sh);
-  if (threadIdx.x == 0) partials[((long long)b * kRespSlots + slot) * ntiles + tile] = s;
+  for (int off = 32; off > 0; off >>= 1) tr += __shfl_xor(tr, off, 64);
+  if (lane == 0) partials[((long long)b * kRespSlots + slot) * ntiles + tile] = tr;
 }
 
-__global__ void finalize_kernel(int batch, int ntiles, int nslots, const double* __restrict__ partials,
-                                double scale, int phase, double* __restrict__ resp, long long resp_stride,
-                                long long resp_offset, int* flag) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// One wave per response sample: its lanes sum the partials (lane by lane in
+// order, then a butterfly).
+__global__ void __launch_bounds__(kBlock)
+    finalize_kernel(int ntiles, int nslots, const double* __restrict__ partials, double scale, int phase,
+                    double* __restrict__ resp, long long resp_stride, long long resp_offset, int* flag) {
+  const int lane = threadIdx.x & 63;
+  const int j = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   const int b = blockIdx.y;
-  if (j >= nslots || b >= batch) return;
+  if (j >= nslots) return;
   const double* p = partials + ((long long)b * kRespSlots + j) * ntiles;
   double s = 0.0;
-  for (int t = 0; t < ntiles; ++t) s += p[t];
+  for (int t = lane; t < ntiles; t += 64) s += p[t];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (lane != 0) return;
   s *= scale;
   const cx<double> w = dophase(s, 0.0, phase);
   if (resp) {
@@ -554,7 +559,7 @@ hipError_t launch_trace_partials(const GridDesc& g, const void* packed, const do
   DipoleMu m;
   for (int j = 0; j < 3; ++j)
     for (int k = 0; k < 3; ++k) m.m[j][k] = mu[j][k];
-  const dim3 grid(ntiles, g.batch);
+  const dim3 grid((ntiles + kBlock / 64 - 1) / (kBlock / 64), g.batch);
 #define F(T, NS) hipLaunchKernelGGL((trace_kernel<T, NS>), grid, dim3(kBlock), 0, s, g, \
                                     static_cast<const T*>(packed), m, tq, ntiles, partials, slot)
   QHFPE_DISPATCH(g, F);
@@ -564,8 +569,8 @@ hipError_t launch_trace_partials(const GridDesc& g, const void* packed, const do
 
 hipError_t launch_finalize(int batch, int ntiles, int nslots, const double* partials, double scale, int phase,
                            double* resp, long long resp_stride, long long resp_offset, int* flag, hipStream_t s) {
-  const dim3 grid((nslots + 63) / 64, batch);
-  hipLaunchKernelGGL(finalize_kernel, grid, dim3(64), 0, s, batch, ntiles, nslots, partials, scale, phase, resp,
+  const dim3 grid((nslots + kBlock / 64 - 1) / (kBlock / 64), batch);
+  hipLaunchKernelGGL(finalize_kernel, grid, dim3(kBlock), 0, s, ntiles, nslots, partials, scale, phase, resp,
                      resp_stride, resp_offset, flag);
   return hipGetLastError();
 }

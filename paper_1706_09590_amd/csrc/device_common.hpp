@@ -6,6 +6,16 @@
 
 namespace qhfpe {
 
+// The stage kernels promise that a column's results do not depend on the
+// launch it is computed in (members of a batch, groups, columns per wave), bit
+// for bit.  The compiler may therefore not choose where it fuses a multiply
+// and an add: contraction is off in their arithmetic, and the fused
+// operations are written out.
+#pragma clang fp contract(off)
+
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 template <typename T>
 struct cx {
   T re, im;
@@ -17,11 +27,11 @@ template <typename T>
 __device__ __forceinline__ cx<T> operator-(cx<T> a, cx<T> b) { return {a.re - b.re, a.im - b.im}; }
 template <typename T>
 __device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b) {
-  return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
+  return {fma_(a.re, b.re, -(a.im * b.im)), fma_(a.re, b.im, a.im * b.re)};
 }
 template <typename T>
 __device__ __forceinline__ cx<T> cmulc(cx<T> a, cx<T> b) {  // a * conj(b)
-  return {a.re * b.re + a.im * b.im, a.im * b.re - a.re * b.im};
+  return {fma_(a.re, b.re, a.im * b.im), fma_(a.im, b.re, -(a.re * b.im))};
 }
 
 // cos and sin of 2 pi e / 48, e = 0..47 (every radix used below divides 48).
@@ -72,7 +82,7 @@ __device__ __forceinline__ cx<T> rot48(cx<T> x) {
   } else {
     const T c = T(kCos48[e]);
     const T s = T(kSin48[e]);
-    return {x.re * c - x.im * s, x.re * s + x.im * c};
+    return {fma_(x.re, c, -(x.im * s)), fma_(x.re, s, x.im * c)};
   }
 }
 
@@ -101,13 +111,12 @@ struct SmallDft<3, S, T> {
   __device__ __forceinline__ static void run(cx<T>* x) {
     const T h = T(0.8660254037844386);  // sin(2 pi / 3)
     cx<T> t1 = x[1] + x[2];
-    cx<T> t2 = {x[0].re - T(0.5) * t1.re, x[0].im - T(0.5) * t1.im};
+    cx<T> t2 = {fma_(T(-0.5), t1.re, x[0].re), fma_(T(-0.5), t1.im, x[0].im)};
     cx<T> d = x[1] - x[2];
-    // S i h d
-    cx<T> t3 = {-T(S) * h * d.im, T(S) * h * d.re};
     x[0] = x[0] + t1;
-    x[1] = t2 + t3;
-    x[2] = t2 - t3;
+    // t2 +- S i h d
+    x[1] = {fma_(-T(S) * h, d.im, t2.re), fma_(T(S) * h, d.re, t2.im)};
+    x[2] = {fma_(T(S) * h, d.im, t2.re), fma_(-T(S) * h, d.re, t2.im)};
   }
 };
 
@@ -170,6 +179,8 @@ struct SmallDft {
   }
 };
 
+#pragma clang fp contract(fast)
+
 // ---------------------------------------------------------------------------
 // Buffer-resource memory access: a 32-bit per-lane byte offset (voffset)
 // plus a wave-uniform byte offset (soffset) from a uniform base, with the
@@ -206,6 +217,7 @@ __device__ __forceinline__ void buf_store(double v, rsrc_t r, unsigned voff, uns
 // this compiler shrink the load to one dword at offset 0 (every element
 // then reads element 0).
 typedef float qhfpe_f2 __attribute__((ext_vector_type(2)));
+typedef float qhfpe_f3 __attribute__((ext_vector_type(3)));
 typedef float qhfpe_f4 __attribute__((ext_vector_type(4)));
 typedef double qhfpe_d2 __attribute__((ext_vector_type(2)));
 template <typename T>
@@ -222,31 +234,68 @@ __device__ __forceinline__ Quad<double> buf_load4(rsrc_t r, unsigned voff, unsig
       __builtin_bit_cast(qhfpe_d2, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff + 16, (int)soff, 0));
   return {{x[0], x[1], y[0], y[1]}};
 }
-// CPOL: cache policy of the store (0, or kStoreNT for non-temporal stores)
+// Stores.  CPOL: cache policy (0, or kStoreNT for non-temporal stores).  A store
+// of more than 8 bytes reads its data registers after it has issued, and a
+// vector instruction right behind it must not overwrite them.  The compiler
+// keeps that distance only where the scalar offset is not a register; with one
+// it put an overwrite directly behind the store, and the GPU then stored the
+// overwritten value (seen in a few lanes of one instantiation, when the
+// memory pipeline was busy).  Wide stores therefore add the scalar offset to
+// the lane offset.
 constexpr int kStoreNT = 2;  // the nt bit of the buffer instructions' cache policy
 template <int CPOL = 0>
-__device__ __forceinline__ void buf_store4(const Quad<float>& q, rsrc_t r, unsigned voff, unsigned soff) {
+__device__ __forceinline__ void buf_store16(qhfpe_f4 x, rsrc_t r, unsigned voff) {
   using u4 = decltype(__builtin_amdgcn_raw_buffer_load_b128(r, 0, 0, 0));
-  const qhfpe_f4 x = {q.v[0], q.v[1], q.v[2], q.v[3]};
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, x), r, (int)voff, (int)soff, CPOL);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, x), r, (int)voff, 0, CPOL);
 }
 template <int CPOL = 0>
-__device__ __forceinline__ void buf_store4(const Quad<double>& q, rsrc_t r, unsigned voff, unsigned soff) {
+__device__ __forceinline__ void buf_store16(qhfpe_d2 x, rsrc_t r, unsigned voff) {
   using u4 = decltype(__builtin_amdgcn_raw_buffer_load_b128(r, 0, 0, 0));
-  const qhfpe_d2 x = {q.v[0], q.v[1]}, y = {q.v[2], q.v[3]};
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, x), r, (int)voff, (int)soff, CPOL);
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, y), r, (int)voff + 16, (int)soff, CPOL);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, x), r, (int)voff, 0, CPOL);
+}
+// M consecutive elements per lane (M = 1..4) in one or two accesses; voff
+// aligned to the element.
+template <int M, int CPOL = 0>
+__device__ __forceinline__ void buf_store_n(const float* v, rsrc_t r, unsigned voff, unsigned soff) {
+  static_assert(M >= 1 && M <= 4, "1 to 4 floats");
+  if constexpr (M == 1) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v[0]), r, (int)voff, (int)soff, CPOL);
+  } else if constexpr (M == 2) {
+    using u2 = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0));
+    const qhfpe_f2 x = {v[0], v[1]};
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, x), r, (int)voff, (int)soff, CPOL);
+  } else if constexpr (M == 3) {
+    using u3 = decltype(__builtin_amdgcn_raw_buffer_load_b96(r, 0, 0, 0));
+    const qhfpe_f3 x = {v[0], v[1], v[2]};
+    __builtin_amdgcn_raw_buffer_store_b96(__builtin_bit_cast(u3, x), r, (int)(voff + soff), 0, CPOL);
+  } else {
+    buf_store16<CPOL>(qhfpe_f4{v[0], v[1], v[2], v[3]}, r, voff + soff);
+  }
+}
+template <int M, int CPOL = 0>
+__device__ __forceinline__ void buf_store_n(const double* v, rsrc_t r, unsigned voff, unsigned soff) {
+  static_assert(M >= 1 && M <= 4, "1 to 4 doubles");
+  using u2 = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0));
+  if constexpr (M >= 2) buf_store16<CPOL>(qhfpe_d2{v[0], v[1]}, r, voff + soff);
+  if constexpr (M == 4) buf_store16<CPOL>(qhfpe_d2{v[2], v[3]}, r, voff + soff + 16);
+  if constexpr (M % 2 == 1)
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v[M - 1]), r, (int)voff + 8 * (M - 1), (int)soff, CPOL);
 }
 
-// M consecutive elements per lane (M * sizeof(T) = 8, 16 or 32 bytes; voff
-// aligned to that size, at most 16).
+// M consecutive elements per lane, M = 1..4, in one or two accesses of at most
+// 16 bytes; voff aligned to the element.
 template <int M>
 __device__ __forceinline__ void buf_load_n(rsrc_t r, unsigned voff, unsigned soff, float* out) {
-  static_assert(M == 2 || M == 4, "2 or 4 floats");
-  if constexpr (M == 2) {
+  static_assert(M >= 1 && M <= 4, "1 to 4 floats");
+  if constexpr (M == 1) {
+    out[0] = buf_load<float>(r, voff, soff);
+  } else if constexpr (M == 2) {
     const qhfpe_f2 x = __builtin_bit_cast(qhfpe_f2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
     out[0] = x[0];
     out[1] = x[1];
+  } else if constexpr (M == 3) {
+    const qhfpe_f3 x = __builtin_bit_cast(qhfpe_f3, __builtin_amdgcn_raw_buffer_load_b96(r, (int)voff, (int)soff, 0));
+    for (int j = 0; j < 3; ++j) out[j] = x[j];
   } else {
     const Quad<float> q = buf_load4(r, voff, soff, 0.0f);
     for (int j = 0; j < 4; ++j) out[j] = q.v[j];
@@ -254,31 +303,57 @@ __device__ __forceinline__ void buf_load_n(rsrc_t r, unsigned voff, unsigned sof
 }
 template <int M>
 __device__ __forceinline__ void buf_load_n(rsrc_t r, unsigned voff, unsigned soff, double* out) {
-  static_assert(M == 2 || M == 4, "2 or 4 doubles");
-  if constexpr (M == 2) {
+  static_assert(M >= 1 && M <= 4, "1 to 4 doubles");
+  if constexpr (M == 1) {
+    out[0] = buf_load<double>(r, voff, soff);
+  } else if constexpr (M <= 3) {
     const qhfpe_d2 x = __builtin_bit_cast(qhfpe_d2, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
     out[0] = x[0];
     out[1] = x[1];
+    if constexpr (M == 3) out[2] = buf_load<double>(r, voff + 16, soff);
   } else {
     const Quad<double> q = buf_load4(r, voff, soff, 0.0);
     for (int j = 0; j < 4; ++j) out[j] = q.v[j];
   }
 }
 
-// Cross-lane rotations over the whole 64-lane wave (DPP wave_ror:1 /
-// wave_rol:1): lane_prev returns lane l-1's value (lane 0 gets lane 63's),
-// lane_next lane l+1's (lane 63 gets lane 0's).
-__device__ __forceinline__ int dpp_prev(int x) { return __builtin_amdgcn_mov_dpp(x, 0x13C, 0xf, 0xf, false); }
-__device__ __forceinline__ int dpp_next(int x) { return __builtin_amdgcn_mov_dpp(x, 0x134, 0xf, 0xf, false); }
-__device__ __forceinline__ float lane_prev(float x) { return __builtin_bit_cast(float, dpp_prev(__builtin_bit_cast(int, x))); }
-__device__ __forceinline__ float lane_next(float x) { return __builtin_bit_cast(float, dpp_next(__builtin_bit_cast(int, x))); }
-__device__ __forceinline__ double lane_prev(double x) {
-  const auto v = __builtin_bit_cast(int __attribute__((ext_vector_type(2))), x);
-  return __builtin_bit_cast(double, (int __attribute__((ext_vector_type(2)))){dpp_prev(v[0]), dpp_prev(v[1])});
+// Cross-lane rotations within groups of L consecutive lanes (L = 16, 32 or 64):
+// lane_prev returns the previous lane's value (the group's first lane gets
+// its last lane's), lane_next the next lane's.  DPP rotations of the wave or of
+// a row of 16 lanes; groups of 32 have none and go through ds_bpermute.
+template <int L>
+__device__ __forceinline__ int lane_prev_b32(int x) {
+  static_assert(L == 16 || L == 32 || L == 64, "group size");
+  if constexpr (L == 64) return __builtin_amdgcn_mov_dpp(x, 0x13C, 0xf, 0xf, false);  // wave_ror:1
+  if constexpr (L == 16) return __builtin_amdgcn_mov_dpp(x, 0x121, 0xf, 0xf, false);  // row_ror:1
+  const int lane = threadIdx.x & 63;
+  return __builtin_amdgcn_ds_bpermute(4 * ((lane & ~31) | ((lane - 1) & 31)), x);
 }
+template <int L>
+__device__ __forceinline__ int lane_next_b32(int x) {
+  if constexpr (L == 64) return __builtin_amdgcn_mov_dpp(x, 0x134, 0xf, 0xf, false);  // wave_rol:1
+  if constexpr (L == 16) return __builtin_amdgcn_mov_dpp(x, 0x12F, 0xf, 0xf, false);  // row_ror:15
+  const int lane = threadIdx.x & 63;
+  return __builtin_amdgcn_ds_bpermute(4 * ((lane & ~31) | ((lane + 1) & 31)), x);
+}
+typedef int qhfpe_i2 __attribute__((ext_vector_type(2)));
+template <int L = 64>
+__device__ __forceinline__ float lane_prev(float x) {
+  return __builtin_bit_cast(float, lane_prev_b32<L>(__builtin_bit_cast(int, x)));
+}
+template <int L = 64>
+__device__ __forceinline__ float lane_next(float x) {
+  return __builtin_bit_cast(float, lane_next_b32<L>(__builtin_bit_cast(int, x)));
+}
+template <int L = 64>
+__device__ __forceinline__ double lane_prev(double x) {
+  const auto v = __builtin_bit_cast(qhfpe_i2, x);
+  return __builtin_bit_cast(double, (qhfpe_i2){lane_prev_b32<L>(v[0]), lane_prev_b32<L>(v[1])});
+}
+template <int L = 64>
 __device__ __forceinline__ double lane_next(double x) {
-  const auto v = __builtin_bit_cast(int __attribute__((ext_vector_type(2))), x);
-  return __builtin_bit_cast(double, (int __attribute__((ext_vector_type(2)))){dpp_next(v[0]), dpp_next(v[1])});
+  const auto v = __builtin_bit_cast(qhfpe_i2, x);
+  return __builtin_bit_cast(double, (qhfpe_i2){lane_next_b32<L>(v[0]), lane_next_b32<L>(v[1])});
 }
 
 // Orders LDS accesses of one wave: accesses before it (of any lane) are
@@ -326,8 +401,8 @@ __device__ __forceinline__ void commutator_mi(const T A[NS][NS], const T* h, T* 
       for (int l = 0; l < NS; ++l) {
         cx<T> hl = herm_get<NS>(h, l, k);
         cx<T> hr = herm_get<NS>(h, j, l);
-        c.re += A[j][l] * hl.re - hr.re * A[l][k];
-        c.im += A[j][l] * hl.im - hr.im * A[l][k];
+        c.re = fma_(-hr.re, A[l][k], fma_(A[j][l], hl.re, c.re));
+        c.im = fma_(-hr.im, A[l][k], fma_(A[j][l], hl.im, c.im));
       }
       // -i c
       if (j == k) {

@@ -48,7 +48,8 @@ struct Layout {
   int n1 = 0, n2 = 0;
   size_t total = 0;
   size_t red_count = 0;
-  int max_tiles = 0;  // tiles per level at the narrowest tile variant
+  int max_tiles = 0;  // trace partials per member and slot: one per tile of the narrowest workgroup
+                      // variant, or one per column where the wave variant exists
 };
 
 int validate(const qhfpe_params* p) {
@@ -100,10 +101,8 @@ Layout make_layout(const qhfpe_params* p) {
   L.level_elems = L.comp_elems * nc;
   L.member_elems = L.level_elems * (p->depth + 1);
   L.state_bytes = align_up((size_t)L.member_elems * p->batch * L.elem);
-  const int esz = (p->precision == QHFPE_FP64) ? 8 : 4;
-  const bool wave_ok = wave_variant_supported(esz, p->n_states, p->np);
-  const int min_tq = wave_ok ? std::min(plan_groups(p->np) * kMinCpt, wave_columns_of(p->n_states, p->np))
-                             : plan_groups(p->np) * kMinCpt;
+  const bool wave_ok = wave_exists(p->np);
+  const int min_tq = wave_ok ? 1 : plan_groups(p->np) * kMinCpt;
   L.max_tiles = (p->nq + min_tq - 1) / min_tq;
   const long long cells = (long long)(p->depth + 1) * p->nq * p->np;
   const long long pack_blocks = (cells + kBlock - 1) / kBlock;
@@ -257,11 +256,11 @@ bool multiplier_tables(const qhfpe_params& p, const Surfaces& U, double dq, doub
 
 // The multiplier tables of the wave variant in one array, each q row
 // permuted so that the n2 values m = k1 + n1 k2 (k2 = 0..n2-1) of row k1
-// are contiguous.  Two states: dtab 0, dtab 1, the coherence table halved
-// (the kernel treats it as a pair of equal diagonal multipliers),
-// U_01(q + r/2) and U_01(q - r/2) (used only for a q-dependent coupling).
-// Three states: dtab 0..2, then the coherence tables of the pairs (0,1),
-// (0,2), (1,2) halved.
+// are contiguous.  The packed diagonals (0, 1) of a column need the sum and
+// the difference of their tables.  Two states: dtab 0 + dtab 1, dtab 0 - dtab 1,
+// the coherence table, U_01(q + r/2) and U_01(q - r/2) (used only for a
+// q-dependent coupling).  Three states: the same sum and difference, dtab 2,
+// then the coherence tables of the pairs (0,1), (0,2), (1,2).
 void wave_tables(const qhfpe_params& p, int n1, int n2, const std::vector<double>& dtab,
                  const std::vector<double>& gtab, const std::vector<double>& ctab, std::vector<double>& mtab) {
   const int nq = p.nq, np = p.np, ns = p.n_states;
@@ -274,12 +273,14 @@ void wave_tables(const qhfpe_params& p, int n1, int n2, const std::vector<double
         for (int k2 = 0; k2 < n2; ++k2) {
           const size_t src = (size_t)i * np + k1 + n1 * k2;
           double v;
-          if (t < ns)
-            v = dtab[t * plane + src];
-          else if (ns == 3 || t == 2)
-            v = 0.5 * gtab[(t - ns) * plane + src];
+          if (t == 0)
+            v = dtab[src] + dtab[plane + src];
+          else if (t == 1)
+            v = dtab[src] - dtab[plane + src];
+          else if (ns == 3)
+            v = t == 2 ? dtab[2 * plane + src] : gtab[(t - 3) * plane + src];
           else
-            v = ctab[(t - 3) * plane + src];
+            v = t == 2 ? gtab[src] : ctab[(t - 3) * plane + src];
           mtab[t * plane + (size_t)i * np + (size_t)k1 * n2 + k2] = v;
         }
 }
@@ -393,18 +394,44 @@ struct qhfpe_handle {
     return hipSuccess;
   }
 
-  bool wave() const { return cpt == kTileWave; }
+  // The wave variant computes tile code 1 (np = 128, 256); at the other np
+  // that it covers it computes the default code (a q-dependent coupling's code
+  // where there is one).
+  bool wave() const {
+    if (cpt == kTileWave) return true;
+    if (!wave_exists(p.np) || wave_variant_supported((int)L.elem, ns, p.np)) return false;
+    return qcoup ? ns == 2 && cpt == kQcCpt : cpt == cpt_default((int)L.elem, ns);
+  }
   // variants that take a q-dependent coupling: the two-state wave variant
   // and the workgroup variant with kQcCpt cells per thread
   bool qc_variant(int code) const { return code == kTileWave ? ns == 2 : code == kQcCpt; }
-  int tq_of(int np, int code) const {
-    return code == kTileWave ? wave_columns_of(ns, np) : plan_groups(np) * code;
+  // levels of all members
+  long long all_levels() const { return mixed ? hmlev[p.batch] : (long long)levels * p.batch; }
+  // whether the stages write their outputs non-temporally: the three state
+  // arrays of the step against the MI355X's 256 MB memory-side cache (measured:
+  // 1024-member 128x128 depth-6 FP32 launch 1248 -> 1201 us; at 113 MB, two
+  // 256x256 depth-8 FP64 members, the same stores cost 17%).  Counted are the
+  // levels the stages touch.
+  bool stream_out() const {
+    constexpr double kMemorySideCacheBytes = 256.0 * 1024 * 1024;
+    return 3.0 * (double)all_levels() * L.level_elems * L.elem > kMemorySideCacheBytes;
   }
-  int tq() const { return tq_of(p.np, cpt); }
-  // the trace partials hold L.max_tiles tiles per member and slot: a variant
-  // with narrower tiles would index past them
-  bool tile_fits(int code) const { return (p.nq + tq_of(p.np, code) - 1) / tq_of(p.np, code) <= L.max_tiles; }
+  // one shape for all of the handle's launches, whatever their member groups
+  WaveShape shape() const {
+    const long long columns = (p.nq + wave_groups(p.np) - 1) / wave_groups(p.np);
+    return wave_shape((int)L.elem, ns, p.np, qcoup != 0, all_levels() * columns, stream_out());
+  }
+  // q columns per unit of a stage launch
+  int tq() const { return wave() ? wave_columns_of(p.np, shape().c) : plan_groups(p.np) * cpt; }
   int ntiles() const { return (p.nq + tq() - 1) / tq(); }
+  // columns per trace partial, partials per member and slot
+  int partial_columns() const { return wave() ? 1 : tq(); }
+  int npartials() const { return (p.nq + partial_columns() - 1) / partial_columns(); }
+  // the trace partials hold L.max_tiles per member and slot: a variant with
+  // more would index past them
+  bool tile_fits(int code) const {
+    return wave_exists(p.np) || (p.nq + plan_groups(p.np) * code - 1) / (plan_groups(p.np) * code) <= L.max_tiles;
+  }
   double dq = 0, dp = 0;
 
   void* y() const { return ws + L.off_y; }
@@ -453,7 +480,7 @@ struct qhfpe_handle {
     a.dtab = dtab();
     a.gtab = gtab();
     a.ctab = ctab();
-    a.mtab = wave_variant_supported((int)L.elem, ns, p.np) ? mtab() : nullptr;
+    a.mtab = wave_exists(p.np) ? mtab() : nullptr;
     a.qcoup = qcoup;
     a.bath = bath();
     a.psym = psym();
@@ -467,17 +494,13 @@ struct qhfpe_handle {
     a.lev_member = mixed ? lev_member() : nullptr;
     a.mfirst = 0;
     a.nblocks_padded = padded_blocks(0, p.batch);
-    a.wpb = wave_wpb(0, p.batch);
-    // the three state arrays of the step against the MI355X's 256 MB
-    // memory-side cache: above it, the stage outputs are stored
-    // non-temporally (measured: 1024-member 128x128 depth-6 FP32 launch
-    // 1248 -> 1201 us; at 113 MB, two 256x256 depth-8 FP64 members, the
-    // same stores cost 17%)
-    // (the levels the stages touch: with per-member depths, fewer than the
-    // handle holds)
-    constexpr double kMemorySideCacheBytes = 256.0 * 1024 * 1024;
-    const double touched = (double)(mixed ? hmlev[p.batch] : (long long)levels * p.batch) * L.level_elems;
-    a.stream_out = 3.0 * touched * L.elem > kMemorySideCacheBytes ? 1 : 0;
+    if (wave()) a.shape = shape();
+    a.npartials = npartials();
+    a.by_levels = FixedDiv::by(levels);
+    a.by_tiles = FixedDiv::by(a.ntiles);
+    a.inv_60dq = 1.0 / (60.0 * dq);
+    a.inv_12dp = 1.0 / (12.0 * dp);
+    a.stream_out = stream_out() ? 1 : 0;
     a.member_stride = L.member_elems;
     a.level_stride = L.level_elems;
     a.comp_stride = L.comp_elems;
@@ -494,20 +517,12 @@ struct qhfpe_handle {
     return a;
   }
 
-  // waves per workgroup of a wave-variant launch over members first ..
-  // first + count - 1
-  int wave_wpb(int first, int count) const {
-    const long long tasks = units(first, count);
-    if (ns == 3) return wave3_wpb((int)L.elem, p.np, tasks);
-    return (!qcoup && tasks <= kWaveSmallTasks) ? kWaveTasksPerBlockSmall : kWaveTasksPerBlock;
-  }
-
   // grid of a stage launch over members first .. first + count - 1,
   // rounded up to a multiple of 8
   int padded_blocks(int first, int count) const {
     const long long u = units(first, count);  // workgroups, or waves of the wave variant
-    const int wpb = wave_wpb(first, count);
-    const long long blocks = wave() ? (u + wpb - 1) / wpb : u;
+    const int wpb = wave() ? shape().wpb : 1;
+    const long long blocks = (u + wpb - 1) / wpb;
     return (int)((blocks + 7) / 8 * 8);
   }
 
@@ -519,11 +534,10 @@ struct qhfpe_handle {
     a.out = static_cast<char*>(a.out) + off;
     if (a.closure) a.closure = static_cast<const char*>(a.closure) + (size_t)first * L.level_elems * L.elem;
     a.bath += (long long)kBathStride * first;
-    if (a.partials) a.partials += (long long)first * kRespSlots * a.ntiles;
+    if (a.partials) a.partials += (long long)first * kRespSlots * a.npartials;
     a.batch = count;
     if (a.mlev) a.mfirst = first;
     a.nblocks_padded = padded_blocks(first, count);
-    a.wpb = wave_wpb(first, count);
     return a;
   }
 
@@ -538,12 +552,11 @@ struct qhfpe_handle {
                                           const_cast<void*>(a.closure), L.level_elems, s);
       if (e != hipSuccess) return e;
     }
-    if (wave() && ns == 3)
-      return p.precision == QHFPE_FP64 ? launch_stage_wave3_f64(p.np, a, nblocks, s)
-                                       : launch_stage_wave3_f32(p.np, a, nblocks, s);
-    if (wave())
-      return p.precision == QHFPE_FP64 ? launch_stage_wave_f64(p.np, a, nblocks, s)
-                                       : launch_stage_wave_f32(p.np, a, nblocks, s);
+    if (wave()) {
+      if (p.precision == QHFPE_FP64)
+        return ns == 2 ? launch_stage_wave_f64_ns2(p.np, a, nblocks, s) : launch_stage_wave_f64_ns3(p.np, a, nblocks, s);
+      return ns == 2 ? launch_stage_wave_f32_ns2(p.np, a, nblocks, s) : launch_stage_wave_f32_ns3(p.np, a, nblocks, s);
+    }
     if (p.precision == QHFPE_FP64)
       return ns == 2 ? launch_stage_f64_ns2(p.np, cpt, a, nblocks, s)
                      : launch_stage_f64_ns3(p.np, cpt, a, nblocks, s);
@@ -571,12 +584,13 @@ int check_handle(const qhfpe_t* h) {
 
 // partial sums of the level-0 trace of y into slot, then (optionally) finalise
 int trace_into(qhfpe_t* h, int slot) {
-  HIP_TRY(launch_trace_partials(h->grid(), h->y(), h->p.mu, h->tq(), h->ntiles(), h->partials(), slot, h->stream));
+  HIP_TRY(launch_trace_partials(h->grid(), h->y(), h->p.mu, h->partial_columns(), h->npartials(), h->partials(), slot,
+                                h->stream));
   return QHFPE_OK;
 }
 
 int finalize(qhfpe_t* h, int nslots, double* resp, long long resp_stride, long long offset) {
-  HIP_TRY(launch_finalize(h->p.batch, h->ntiles(), nslots, h->partials(), h->dq * h->dp, h->phase, resp,
+  HIP_TRY(launch_finalize(h->p.batch, h->npartials(), nslots, h->partials(), h->dq * h->dp, h->phase, resp,
                           resp_stride, offset, h->flag(), h->stream));
   return QHFPE_OK;
 }
@@ -584,7 +598,8 @@ int finalize(qhfpe_t* h, int nslots, double* resp, long long resp_stride, long l
 // finalize for members first .. first + count - 1 on stream s
 int finalize_members(qhfpe_t* h, int first, int count, int nslots, double* resp, long long resp_stride,
                      long long offset, hipStream_t s) {
-  HIP_TRY(launch_finalize(count, h->ntiles(), nslots, h->partials() + (long long)first * kRespSlots * h->ntiles(),
+  HIP_TRY(launch_finalize(count, h->npartials(), nslots,
+                          h->partials() + (long long)first * kRespSlots * h->npartials(),
                           h->dq * h->dp, h->phase, resp ? resp + (long long)first * resp_stride : nullptr,
                           resp_stride, offset, h->flag(), s));
   return QHFPE_OK;
@@ -629,7 +644,7 @@ int install_surfaces(qhfpe_t* h, const Surfaces& U) {
   double coup[QHFPE_MAX_STATES][QHFPE_MAX_STATES];
   if (!multiplier_tables(h->p, U, h->dq, h->dp, dt, gt, ct, &coup_const, coup))
     return fail(QHFPE_EINVAL, "the potential has a non-finite value on the grid");
-  if (wave_variant_supported((int)h->L.elem, h->ns, h->p.np)) wave_tables(h->p, h->L.n1, h->L.n2, dt, gt, ct, mt);
+  if (wave_exists(h->p.np)) wave_tables(h->p, h->L.n1, h->L.n2, dt, gt, ct, mt);
   hipError_t e = hipSuccess;
   auto up = [&](void* dst, const std::vector<double>& src) {
     if (e != hipSuccess || src.empty()) return;

@@ -21,7 +21,7 @@ struct Plan {
 };
 constexpr Plan kPlans[] = {
     {8, 4, 2},   {12, 4, 3},  {16, 4, 4},   {24, 6, 4},    {32, 8, 4},    {48, 8, 6},
-    {64, 8, 8},  {96, 12, 8}, {128, 16, 8}, {192, 16, 12}, {256, 16, 16},
+    {64, 8, 8},  {96, 8, 12}, {128, 16, 8}, {192, 16, 12}, {256, 16, 16},
 };
 inline const Plan* find_plan(int np) {
   for (const Plan& p : kPlans)
@@ -48,38 +48,93 @@ inline bool cpt_supported(int elem_bytes, int ns, int cpt) { return cpt_supporte
 // 256-thread workgroup leaves room for one workgroup per CU at np = 256).
 inline int cpt_default(int /*elem_bytes*/, int ns) { return (ns == 3) ? 2 : 4; }
 
-// Tile code of the wave-independent stage variant (stage_wave.hpp): one
-// wave per 512/np q columns, two states and np = 128 or 256.
+// Tile code of the wave-independent stage variant (stage_wave.hpp) at np = 128
+// and 256; at the other np that it covers it computes the default code.
 constexpr int kTileWave = 1;
 constexpr int kMaxGroups = 4;  // member groups (streams) of qhfpe_step
-constexpr int kWaveTables = 5;  // multiplier planes of the wave variant
-// Waves per workgroup of the wave variant: four share the twiddle and symbol
-// tables in LDS; launches of at most kWaveSmallTasks tasks (one round on the
-// GPU) use two, whose finer workgroups spread the waves more evenly over the
-// CUs and so shorten the launch's tail.
-constexpr int kWaveTasksPerBlock = 4;
-constexpr int kWaveTasksPerBlockSmall = 2;
-constexpr int kWaveSmallTasks = 2048;
-inline bool wave_supported(int ns, int np) { return ns == 2 && (np == 128 || np == 256); }
-// q columns per task of the wave variant (a lane holds np / 64 p nodes)
-constexpr int wave_columns(int np) { return 512 / np; }
-// The three-state wave variant (stage_wave3.hpp): np = 128 or 256, constant
-// couplings only, six multiplier planes; two q columns per task at np = 128,
-// one at np = 256 (LDS: 11 KB per FP32 wave instead of 20).
-constexpr int wave3_columns(int np) { return np == 256 ? 1 : 2; }
+// Multiplier planes of the wave variant: two states 5, three states 6.
+constexpr int kWaveTables = 5;
 constexpr int kWaveTables3 = 6;
-inline bool wave3_supported(int /*elem_bytes*/, int np) { return np == 128 || np == 256; }
-inline bool wave_variant_supported(int elem_bytes, int ns, int np) {
-  return ns == 2 ? wave_supported(ns, np) : wave3_supported(elem_bytes, np);
-}
-inline int wave_columns_of(int ns, int np) { return ns == 3 ? wave3_columns(np) : wave_columns(np); }
 inline int wave_table_planes(int ns) { return ns == 3 ? kWaveTables3 : kWaveTables; }
-// Waves per workgroup of a three-state wave launch of `tasks` tasks: four
-// only for large FP32 launches (an FP64 four-wave group's LDS would leave
-// room for one group per CU).
-inline int wave3_wpb(int elem_bytes, int /*np*/, long long tasks) {
-  return (elem_bytes == 4 && tasks > kWaveSmallTasks) ? kWaveTasksPerBlock : kWaveTasksPerBlockSmall;
+// p nodes per lane of the wave variant (a column lies on np / wave_nodes
+// lanes: 16, 32 or 64); 0 where it does not exist.  Several nodes a lane make
+// wide loads and few lane exchanges; 64 takes one so that a column fills the wave.
+constexpr int wave_nodes(int np) {
+  return np == 256 ? 4 : (np == 192 || np == 96 || np == 48) ? 3 : (np == 128 || np == 32) ? 2 : np == 64 ? 1 : 0;
 }
+constexpr bool wave_exists(int np) { return wave_nodes(np) != 0; }
+// public tile code 1
+inline bool wave_supported(int ns, int np) { return ns == 2 && (np == 128 || np == 256); }
+inline bool wave_variant_supported(int /*elem_bytes*/, int /*ns*/, int np) { return np == 128 || np == 256; }
+// Shape of a wave launch: q columns per lane group, components in flight (or
+// kStaggered), waves per workgroup.
+constexpr int kStaggered = 0;
+struct WaveShape {
+  int c = 0, pf = 0, wpb = 0;
+};
+constexpr int wave_groups(int np) { return 64 * wave_nodes(np) / np; }  // lane groups per wave
+inline int wave_columns_of(int np, int c) { return wave_groups(np) * c; }
+
+// The shape for a handle whose stages would be `waves` waves with one column
+// per lane group.  Results do not depend on it.  One column per wave keeps a
+// wave's chain short (few loads to wait for, one item per FFT round) but loads
+// 7 window columns per column and leaves FFT lanes idle: it wins while the
+// waves find SIMDs of their own.  More columns per wave save loads and fill
+// the FFT rounds, which wins once several waves share a SIMD.  Measured (us
+// per stage launch, one column / two / four per lane group):
+//   two states: 128 FP64, 896 waves 7.6 / 7.9 / 10.6, 2688 waves 11.2 / 10.6 /
+//   -, 7168 waves 21 / 17.5 / 17.4, 28672 waves 97 / 81 / 73; 64 FP32, 1280
+//   waves 6.2 / 6.5 / 8.1, 10240 waves 14.3 / 10.9 / 10.2; 256 FP64, 192 waves
+//   9.0 / 10.1, 2304 waves 21.2 / 18.2; 96 FP64 (two lane groups), 1344 waves
+//   10.3 / 11.4, 5376 waves 23.5 / 19.8 / 32.7.
+//   three states: 128 FP32, 14336 waves 49.5 / 40.6; 256 FP32, 9216 waves
+//   55.6 with one (two would leave LDS for six waves a CU).
+// Components in flight: with SIMDs to spare a one-column wave issues two (three
+// for nine components; in FP32 all four of two states: 64 x 64 5.2 against
+// 5.3 us); otherwise the staggered schedule, except FP32 at 256, whose second
+// register slots would cost it the fourth wave per SIMD (14.2 against 15.1 us).
+// Workgroups: two waves spread more evenly over the CUs, four share the tables
+// (256 FP64 1152 tasks 18.2 against 21.4 us, 9216 tasks 111 against 105 us;
+// at 192 four win throughout).
+inline WaveShape wave_shape(int elem_bytes, int ns, int np, bool qcoup, long long waves, bool stream) {
+  const bool f32 = elem_bytes == 4;
+  if (ns == 3) {
+    const bool pairs = np == 128 || np == 64;  // two columns fit
+    if (pairs && (stream || waves >= 7000)) return {2, kStaggered, 2};
+    if ((f32 || pairs) && !stream && waves <= 2000) return {1, 3, 1};
+    return {1, kStaggered, 2};
+  }
+  if (!stream && waves <= (wave_groups(np) > 1 ? 2800 : 1400)) {
+    if (f32 && !qcoup && waves <= 700) return {1, 4, 1};
+    return {1, 2, 1};
+  }
+  if (np == 256) {
+    const int pf = f32 && !qcoup ? 1 : kStaggered;
+    return {2, pf, stream || waves > 7000 ? 4 : 2};
+  }
+  if (np == 192) return {2, kStaggered, 4};
+  if ((np == 128 && (stream || waves >= 13000)) || (np == 64 && (stream || waves >= 7000))) return {4, kStaggered, 4};
+  return {2, kStaggered, 2};
+}
+
+// Exact division of 0 <= t < 2^31 by a fixed d >= 1 with one high product
+// (round-up method: 2^(32 + s) / d with s = ceil(log2 d), the 2^32 of the
+// multiplier added by hand).
+struct FixedDiv {
+  unsigned mul = 0;
+  int shift = 0;
+  static FixedDiv by(unsigned d) {
+    FixedDiv f;
+    while ((1ull << f.shift) < d) ++f.shift;
+    f.mul = (unsigned)(((1ull << 32) * ((1ull << f.shift) - d)) / d + 1);
+    return f;
+  }
+  __host__ __device__ int div(int t) const {
+    const unsigned u = (unsigned)t;
+    return (int)(((unsigned)(((unsigned long long)mul * u) >> 32) + u) >> shift);
+  }
+};
+
 inline bool tile_supported(int elem_bytes, int ns, int np, int code) {
   return code == kTileWave ? wave_variant_supported(elem_bytes, ns, np) : cpt_supported(elem_bytes, ns, code);
 }
@@ -100,9 +155,9 @@ struct StageArgs {
   const void* gtab;      // [npair][nq][np]: (U_j(q+r/2) - U_k(q-r/2)) / (hbar np), j < k
   const void* ctab;      // [npair][2][nq][np]: U_jl(q + r/2), U_jl(q - r/2) / (hbar np), pair j < l
                          // (q-dependent couplings in the workgroup variant)
-  const void* mtab;      // wave variant: [kWaveTables][nq][n1][n2] = dtab 0, dtab 1, gtab / 2, U_01(q + r/2),
-                         // U_01(q - r/2) (both / (hbar np)), entry (k1, k2) at m = k1 + n1 k2;
-                         // three states: [kWaveTables3][nq][n1][n2] = dtab 0..2, gtab 0..2 / 2
+  const void* mtab;      // wave variant: [kWaveTables][nq][n1][n2] = dtab 0 + dtab 1, dtab 0 - dtab 1, gtab,
+                         // U_01(q + r/2), U_01(q - r/2) (both / (hbar np)), entry (k1, k2) at m = k1 + n1 k2;
+                         // three states: [kWaveTables3][nq][n1][n2] = the same sum and difference, dtab 2, gtab 0..2
   const double* bath;    // [B][kBathStride]: r0/m (= zeta), gamma, c0, c_delta, beta per member
   const void* psym;      // [2][np]: DFT symbols of D_p2 and D_p D_p, divided by np
   const void* closure;   // wave variant: learned W^(N+1) [B][4][nq][np] (one level per member), or nullptr
@@ -122,8 +177,10 @@ struct StageArgs {
   int nblocks_padded;       // grid size: ntiles * (depth+1) * batch rounded up to a multiple of 8
   int stream_out;           // wave variant: 1 = non-temporal output stores (the state exceeds the
                             // memory-side cache)
-  int wpb;                  // wave variant: waves (tasks) per workgroup, kWaveTasksPerBlock or
-                            // kWaveTasksPerBlockSmall
+  WaveShape shape;          // wave variant
+  int npartials;            // trace partials per member and slot (wave variant: one per column)
+  FixedDiv by_levels, by_tiles;  // division by depth + 1 and by ntiles
+  double inv_60dq, inv_12dp;     // 1 / (60 dq), 1 / (12 dp)
   long long member_stride;  // elements per member
   long long level_stride;   // elements per level
   long long comp_stride;    // elements per packed component (nq * np)
@@ -189,10 +246,10 @@ hipError_t launch_stage_f64_ns2(int np, int cpt, const StageArgs& a, int nblocks
 hipError_t launch_stage_f64_ns3(int np, int cpt, const StageArgs& a, int nblocks, hipStream_t s);
 hipError_t launch_stage_f32_ns2(int np, int cpt, const StageArgs& a, int nblocks, hipStream_t s);
 hipError_t launch_stage_f32_ns3(int np, int cpt, const StageArgs& a, int nblocks, hipStream_t s);
-hipError_t launch_stage_wave_f64(int np, const StageArgs& a, int nblocks, hipStream_t s);
-hipError_t launch_stage_wave_f32(int np, const StageArgs& a, int nblocks, hipStream_t s);
-hipError_t launch_stage_wave3_f64(int np, const StageArgs& a, int nblocks, hipStream_t s);
-hipError_t launch_stage_wave3_f32(int np, const StageArgs& a, int nblocks, hipStream_t s);
+hipError_t launch_stage_wave_f64_ns2(int np, const StageArgs& a, int nblocks, hipStream_t s);
+hipError_t launch_stage_wave_f64_ns3(int np, const StageArgs& a, int nblocks, hipStream_t s);
+hipError_t launch_stage_wave_f32_ns2(int np, const StageArgs& a, int nblocks, hipStream_t s);
+hipError_t launch_stage_wave_f32_ns3(int np, const StageArgs& a, int nblocks, hipStream_t s);
 
 // Pointwise and reduction kernels (aux_kernels.hip).
 struct DipoleMu {

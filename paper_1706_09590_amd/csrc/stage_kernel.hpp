@@ -44,7 +44,7 @@ QHFPE_SPLIT(24, 6, 4)
 QHFPE_SPLIT(32, 8, 4)
 QHFPE_SPLIT(48, 8, 6)
 QHFPE_SPLIT(64, 8, 8)
-QHFPE_SPLIT(96, 12, 8)
+QHFPE_SPLIT(96, 8, 12)
 QHFPE_SPLIT(128, 16, 8)
 QHFPE_SPLIT(192, 16, 12)
 QHFPE_SPLIT(256, 16, 16)
@@ -160,15 +160,15 @@ template <bool MIX>
 __device__ __forceinline__ UnitPos unit_pos(const StageArgs& a, int t) {
   UnitPos u;
   if constexpr (!MIX) {
-    const int L = a.depth + 1;
-    u.n = t % L;
-    u.tile = (t / L) % a.ntiles;
-    u.b = t / (L * a.ntiles);
+    const int row = a.by_levels.div(t);
+    u.n = t - row * (a.depth + 1);
+    u.b = a.by_tiles.div(row);
+    u.tile = row - u.b * a.ntiles;
     u.depth = a.depth;
     return u;
   }
   const int tg = t + a.ntiles * a.mlev[a.mfirst];
-  const int bg = a.lev_member[tg / a.ntiles];
+  const int bg = a.lev_member[a.by_tiles.div(tg)];
   const int r0 = a.mlev[bg], L = a.mlev[bg + 1] - r0;
   const int local = tg - a.ntiles * r0;
   u.n = local % L;
@@ -659,7 +659,7 @@ __global__ void __launch_bounds__((PlanOf<T, NS, NP, CPT_>::NT), 2) stage_kernel
     if (tid == 0) {
       double s = 0.0;
       for (int w = 0; w < NW; ++w) s += wsum[w];
-      a.partials[((long long)b * kRespSlots + a.slot) * a.ntiles + tile] = s;
+      a.partials[((long long)b * kRespSlots + a.slot) * a.npartials + tile] = s;
     }
   }
 }
@@ -680,14 +680,23 @@ hipError_t launch_stage_variant(const StageArgs& a, int nblocks, hipStream_t s) 
 }
 
 // a q-dependent coupling has one variant, kQcCpt cells per thread
+// (at np = 32 .. 96 and 192 the wave variant computes the default code, and
+// for two states the q-dependent couplings)
 template <typename T, int NS, int NP>
 hipError_t launch_stage_np(int cpt, const StageArgs& a, int nblocks, hipStream_t s) {
-  if (a.qcoup) return cpt == kQcCpt ? launch_stage_variant<T, NS, NP, kQcCpt, true>(a, nblocks, s) : hipErrorInvalidValue;
+  constexpr bool kWave = wave_exists(NP) && NP != 128 && NP != 256;
+  if (a.qcoup) {
+    if constexpr (!kWave || NS == 3)
+      if (cpt == kQcCpt) return launch_stage_variant<T, NS, NP, kQcCpt, true>(a, nblocks, s);
+    return hipErrorInvalidValue;
+  }
   switch (cpt) {
     case 2:
-      return launch_stage_variant<T, NS, NP, 2>(a, nblocks, s);
+      if constexpr (!kWave || NS == 2) return launch_stage_variant<T, NS, NP, 2>(a, nblocks, s);
+      return hipErrorInvalidValue;
     case 4:
-      return launch_stage_variant<T, NS, NP, 4>(a, nblocks, s);
+      if constexpr (!kWave || NS == 3) return launch_stage_variant<T, NS, NP, 4>(a, nblocks, s);
+      return hipErrorInvalidValue;
     case 8:
       return launch_stage_variant<T, NS, NP, 8>(a, nblocks, s);
     default:
