@@ -34,31 +34,30 @@ __device__ __forceinline__ cx<T> cmulc(cx<T> a, cx<T> b) {  // a * conj(b)
   return {fma_(a.re, b.re, a.im * b.im), fma_(a.im, b.re, -(a.re * b.im))};
 }
 
-// cos and sin of 2 pi e / 48, e = 0..47 (every radix used below divides 48).
+// cos and sin of 2 pi e / 48, e = 0..47 (every radix used below divides 48),
+// correctly rounded, so that conjugate and mirrored angles match bit for bit.
 __device__ constexpr double kCos48[48] = {
-    1.0, 0.9914448613738104, 0.9659258262890683, 0.9238795325112867, 0.8660254037844387,
-    0.7933533402912352, 0.7071067811865476, 0.6087614290087207, 0.5000000000000001,
-    0.38268343236508984, 0.25881904510252074, 0.1305261922200517, 0.0, -0.1305261922200516,
-    -0.25881904510252063, -0.3826834323650895, -0.4999999999999998, -0.6087614290087207,
-    -0.7071067811865475, -0.793353340291235, -0.8660254037844387, -0.9238795325112867,
-    -0.9659258262890682, -0.9914448613738104, -1.0, -0.9914448613738104, -0.9659258262890683,
-    -0.9238795325112868, -0.8660254037844388, -0.7933533402912352, -0.7071067811865479,
-    -0.6087614290087209, -0.5000000000000004, -0.3826834323650895, -0.25881904510252063,
-    -0.13052619222005163, 0.0, 0.13052619222005127, 0.2588190451025203, 0.38268343236508917,
-    0.5000000000000001, 0.6087614290087199, 0.7071067811865474, 0.7933533402912349,
-    0.8660254037844384, 0.9238795325112868, 0.9659258262890681, 0.9914448613738104};
+    1.0, 0.9914448613738104, 0.9659258262890683, 0.9238795325112867, 0.8660254037844386,
+    0.7933533402912352, 0.7071067811865476, 0.6087614290087207, 0.5, 0.3826834323650898,
+    0.25881904510252074, 0.1305261922200516, 0.0, -0.1305261922200516, -0.25881904510252074,
+    -0.3826834323650898, -0.5, -0.6087614290087207, -0.7071067811865476, -0.7933533402912352,
+    -0.8660254037844386, -0.9238795325112867, -0.9659258262890683, -0.9914448613738104, -1.0,
+    -0.9914448613738104, -0.9659258262890683, -0.9238795325112867, -0.8660254037844386,
+    -0.7933533402912352, -0.7071067811865476, -0.6087614290087207, -0.5, -0.3826834323650898,
+    -0.25881904510252074, -0.1305261922200516, 0.0, 0.1305261922200516, 0.25881904510252074,
+    0.3826834323650898, 0.5, 0.6087614290087207, 0.7071067811865476, 0.7933533402912352,
+    0.8660254037844386, 0.9238795325112867, 0.9659258262890683, 0.9914448613738104};
 __device__ constexpr double kSin48[48] = {
-    0.0, 0.13052619222005157, 0.25881904510252074, 0.3826834323650898, 0.49999999999999994,
-    0.6087614290087207, 0.7071067811865475, 0.7933533402912352, 0.8660254037844386,
-    0.9238795325112867, 0.9659258262890683, 0.9914448613738104, 1.0, 0.9914448613738104,
-    0.9659258262890683, 0.9238795325112868, 0.8660254037844387, 0.7933533402912352,
-    0.7071067811865476, 0.6087614290087209, 0.49999999999999994, 0.3826834323650899,
-    0.258819045102521, 0.130526192220052, 0.0, -0.13052619222005177, -0.2588190451025208,
-    -0.38268343236508967, -0.4999999999999997, -0.6087614290087207, -0.7071067811865471,
-    -0.7933533402912349, -0.8660254037844384, -0.9238795325112868, -0.9659258262890683,
-    -0.9914448613738104, -1.0, -0.9914448613738105, -0.9659258262890684, -0.923879532511287,
-    -0.8660254037844386, -0.7933533402912357, -0.7071067811865477, -0.6087614290087209,
-    -0.5000000000000004, -0.38268343236508956, -0.25881904510252157, -0.13052619222005168};
+    0.0, 0.1305261922200516, 0.25881904510252074, 0.3826834323650898, 0.5, 0.6087614290087207,
+    0.7071067811865476, 0.7933533402912352, 0.8660254037844386, 0.9238795325112867, 0.9659258262890683,
+    0.9914448613738104, 1.0, 0.9914448613738104, 0.9659258262890683, 0.9238795325112867,
+    0.8660254037844386, 0.7933533402912352, 0.7071067811865476, 0.6087614290087207, 0.5,
+    0.3826834323650898, 0.25881904510252074, 0.1305261922200516, 0.0, -0.1305261922200516,
+    -0.25881904510252074, -0.3826834323650898, -0.5, -0.6087614290087207, -0.7071067811865476,
+    -0.7933533402912352, -0.8660254037844386, -0.9238795325112867, -0.9659258262890683,
+    -0.9914448613738104, -1.0, -0.9914448613738104, -0.9659258262890683, -0.9238795325112867,
+    -0.8660254037844386, -0.7933533402912352, -0.7071067811865476, -0.6087614290087207, -0.5,
+    -0.3826834323650898, -0.25881904510252074, -0.1305261922200516};
 
 // x * exp(2 pi i E / 48) with the angle known at compile time; multiples of
 // a quarter turn are exact swaps and sign flips.
@@ -73,16 +72,14 @@ __device__ __forceinline__ cx<T> rot48(cx<T> x) {
     return {-x.re, -x.im};
   } else if constexpr (e == 36) {
     return {x.im, -x.re};
-  } else if constexpr (e % 6 == 0) {
-    // odd multiples of an eighth turn: (+-1 +- i)/sqrt(2)
-    const T h = T(0.70710678118654752440);
-    constexpr int cs = (e == 6 || e == 42) ? 1 : -1;
-    constexpr int sn = (e == 6 || e == 18) ? 1 : -1;
-    return {h * (T(cs) * x.re - T(sn) * x.im), h * (T(sn) * x.re + T(cs) * x.im)};
   } else {
-    const T c = T(kCos48[e]);
-    const T s = T(kSin48[e]);
-    return {fma_(x.re, c, -(x.im * s)), fma_(x.re, s, x.im * c)};
+    // (the signs go to the operands, where they cost nothing, so that angles
+    // of one magnitude share their constants)
+    const T c = T(kCos48[e] < 0 ? -kCos48[e] : kCos48[e]);
+    const T s = T(kSin48[e] < 0 ? -kSin48[e] : kSin48[e]);
+    const T cr = kCos48[e] < 0 ? -x.re : x.re, ci = kCos48[e] < 0 ? -x.im : x.im;
+    const T sr = kSin48[e] < 0 ? -x.re : x.re, si = kSin48[e] < 0 ? -x.im : x.im;
+    return {fma_(cr, c, -(si * s)), fma_(sr, s, ci * c)};
   }
 }
 
@@ -324,15 +321,15 @@ __device__ __forceinline__ void buf_load_n(rsrc_t r, unsigned voff, unsigned sof
 template <int L>
 __device__ __forceinline__ int lane_prev_b32(int x) {
   static_assert(L == 16 || L == 32 || L == 64, "group size");
-  if constexpr (L == 64) return __builtin_amdgcn_mov_dpp(x, 0x13C, 0xf, 0xf, false);  // wave_ror:1
-  if constexpr (L == 16) return __builtin_amdgcn_mov_dpp(x, 0x121, 0xf, 0xf, false);  // row_ror:1
+  if constexpr (L == 64) return __builtin_amdgcn_update_dpp(0, x, 0x13C, 0xf, 0xf, true);  // wave_ror:1
+  if constexpr (L == 16) return __builtin_amdgcn_update_dpp(0, x, 0x121, 0xf, 0xf, true);  // row_ror:1
   const int lane = threadIdx.x & 63;
   return __builtin_amdgcn_ds_bpermute(4 * ((lane & ~31) | ((lane - 1) & 31)), x);
 }
 template <int L>
 __device__ __forceinline__ int lane_next_b32(int x) {
-  if constexpr (L == 64) return __builtin_amdgcn_mov_dpp(x, 0x134, 0xf, 0xf, false);  // wave_rol:1
-  if constexpr (L == 16) return __builtin_amdgcn_mov_dpp(x, 0x12F, 0xf, 0xf, false);  // row_ror:15
+  if constexpr (L == 64) return __builtin_amdgcn_update_dpp(0, x, 0x134, 0xf, 0xf, true);  // wave_rol:1
+  if constexpr (L == 16) return __builtin_amdgcn_update_dpp(0, x, 0x12F, 0xf, 0xf, true);  // row_ror:15
   const int lane = threadIdx.x & 63;
   return __builtin_amdgcn_ds_bpermute(4 * ((lane & ~31) | ((lane + 1) & 31)), x);
 }

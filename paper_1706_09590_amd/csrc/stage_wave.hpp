@@ -99,6 +99,65 @@ struct WavePlan {
 template <typename T>
 using lds_cx = T __attribute__((ext_vector_type(2)));
 
+// 16-point DFTs shared by four lanes each, for launches whose waves have idle
+// lanes in the FFT rounds (one lane alone takes 16 points in a chain of about
+// 160 operations).  Item i's points lie at pts(i)[stride k]; sub-lane j of an
+// item computes the j-th four-point DFT of either half of the 4 x 4
+// factorisation, with the operations and constants of SmallDft<16> (the same
+// bits), in two LDS round trips.  out(i, k, X_k) returns what is stored at
+// position k.  A stage of 128 x 64 x 4 levels, one column a wave, takes 5.95 us
+// instead of 6.95 (FP64), 128 x 128 x 7 6.1 instead of 6.6 (FP32).
+template <int S, typename T, typename Pts, typename Out>
+__device__ __forceinline__ void dft16_four_lanes(int lane, int items, int stride, Pts pts, Out out) {
+#pragma clang fp contract(off)
+  const int rounds = (4 * items + 63) / 64;  // (a constant once inlined)
+  const int j = lane & 3;
+  // w16^(j k1), k1 = 1..3
+  T wc[3], ws[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int e1 = 3 * (k + 1), e2 = 6 * (k + 1), e3 = 9 * (k + 1);
+    wc[k] = j == 0 ? T(1) : (j == 1 ? T(kCos48[e1]) : (j == 2 ? T(kCos48[e2]) : T(kCos48[e3])));
+    ws[k] = j == 0 ? T(0) : (j == 1 ? T(S * kSin48[e1]) : (j == 2 ? T(S * kSin48[e2]) : T(S * kSin48[e3])));
+  }
+#pragma unroll
+  for (int t = 0; t < rounds; ++t) {
+    const int item = (lane >> 2) + 16 * t;
+    if (4 * items % 64 == 0 || t + 1 < rounds || item < items) {
+      lds_cx<T>* const z = pts(item) + j * stride;
+      cx<T> x[4];
+#pragma unroll
+      for (int n1 = 0; n1 < 4; ++n1) x[n1] = {z[4 * n1 * stride][0], z[4 * n1 * stride][1]};
+      SmallDft<4, S, T>::run(x);
+#pragma unroll
+      for (int k1 = 1; k1 < 4; ++k1) x[k1] = cmul(x[k1], cx<T>{wc[k1 - 1], ws[k1 - 1]});
+#pragma unroll
+      for (int k1 = 0; k1 < 4; ++k1) z[4 * k1 * stride] = lds_cx<T>{x[k1].re, x[k1].im};
+    }
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int t = 0; t < rounds; ++t) {
+    const int item = (lane >> 2) + 16 * t;
+    const bool on = 4 * items % 64 == 0 || t + 1 < rounds || item < items;
+    cx<T> x[4];
+    if (on) {
+      const lds_cx<T>* const z = pts(item) + 4 * j * stride;
+#pragma unroll
+      for (int n2 = 0; n2 < 4; ++n2) x[n2] = {z[n2 * stride][0], z[n2 * stride][1]};
+      SmallDft<4, S, T>::run(x);
+#pragma unroll
+      for (int k2 = 0; k2 < 4; ++k2) x[k2] = out(item, j + 4 * k2, x[k2]);
+    }
+    wave_lds_sync();  // an item's lanes share a round: all have read
+    if (on) {
+      lds_cx<T>* const z = pts(item) + j * stride;
+#pragma unroll
+      for (int k2 = 0; k2 < 4; ++k2) z[4 * k2 * stride] = lds_cx<T>{x[k2].re, x[k2].im};
+    }
+  }
+}
+
 // C: columns per lane group.  PF: components whose loads are in flight (each
 // holds its window and neighbour levels in registers): component c + PF
 // takes c's registers once c is done; kStaggered: one in flight at the start,
@@ -462,9 +521,20 @@ __global__ void __launch_bounds__(64 * WPB, OCC) stage_wave_kernel(StageArgs a) 
   auto get = [](const lds_cx<T>& x) { return cx<T>{x[0], x[1]}; };
   auto put = [](cx<T> x) { return lds_cx<T>{x.re, x.im}; };
 
+  // small launches share their 16-point DFTs between lanes
+  // where the sub-items fit one round (np = 128).  With more rounds a lone member
+  // of a small grid gains 4% but eight members lose 3 to 8% (192 and 256 points).
+  constexpr bool kShare1 = WPB == 1 && NS == 2 && N1 == 16 && 4 * P1 <= 64;
+  auto strided = [&](int item) { return s + item / N2 * LDP + item % N2; };
+
   // first forward pass: N1-point DFTs over stride N2, twiddle (item: f, n2)
+  if constexpr (kShare1) {
+    dft16_four_lanes<1, T>(lane, P1, N2 + 1, strided, [&](int item, int k1, cx<T> x) {
+      return cmul(x, get(stw[k1 * (N2 + 1) + item % N2]));
+    });
+  }
 #pragma unroll
-  for (int t = 0; t < R1; ++t) {
+  for (int t = 0; t < (kShare1 ? 0 : R1); ++t) {
     const int item = lane + 64 * t;
     if (P1 % 64 == 0 || t + 1 < R1 || item < P1) {
       const int n2 = item % N2;
@@ -506,7 +576,9 @@ __global__ void __launch_bounds__(64 * WPB, OCC) stage_wave_kernel(StageArgs a) 
       }
     }
   }
-  // second forward pass: contiguous N2-point DFTs of row k1 (item: f, k1)
+  // second forward pass: contiguous N2-point DFTs of row k1 (item: f, k1).  Row
+  // 0 also stores X[0] in its padding slot, so that the partner of index m
+  // lies at pbase - k2 for every row
 #pragma unroll
   for (int t = 0; t < R2; ++t) {
     const int item = lane + 64 * t;
@@ -519,8 +591,6 @@ __global__ void __launch_bounds__(64 * WPB, OCC) stage_wave_kernel(StageArgs a) 
       SmallDft<N2, 1, T>::run(x);
 #pragma unroll
       for (int k2 = 0; k2 < N2; ++k2) z[k2] = put(x[k2]);
-      // row 0 also stores X[0] in its padding slot, so that the partner of
-      // index m lies at pbase - k2 for every row
       if (k1 == 0) z[N2] = put(x[0]);
     }
   }
@@ -629,8 +699,9 @@ __global__ void __launch_bounds__(64 * WPB, OCC) stage_wave_kernel(StageArgs a) 
 
   if constexpr (WPB > 1) issue_y();
   // second inverse pass: N1-point DFTs over stride N2, natural order out
+  if constexpr (kShare1) dft16_four_lanes<-1, T>(lane, P1, N2 + 1, strided, [](int, int, cx<T> x) { return x; });
 #pragma unroll
-  for (int t = 0; t < R1; ++t) {
+  for (int t = 0; t < (kShare1 ? 0 : R1); ++t) {
     const int item = lane + 64 * t;
     if (P1 % 64 == 0 || t + 1 < R1 || item < P1) {
       const int n2 = item % N2;
