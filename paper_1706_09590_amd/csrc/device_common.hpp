@@ -239,7 +239,8 @@ __device__ __forceinline__ Quad<double> buf_load4(rsrc_t r, unsigned voff, unsig
 // overwritten value (seen in a few lanes of one instantiation, when the
 // memory pipeline was busy).  Wide stores therefore add the scalar offset to
 // the lane offset.
-constexpr int kStoreNT = 2;  // the nt bit of the buffer instructions' cache policy
+constexpr int kStoreNT = 2;        // the nt bit of the buffer instructions' cache policy
+constexpr int kStoreThrough = 16;  // its sc1 bit: written through the L2, in the scope of the whole device
 template <int CPOL = 0>
 __device__ __forceinline__ void buf_store16(qhfpe_f4 x, rsrc_t r, unsigned voff) {
   using u4 = decltype(__builtin_amdgcn_raw_buffer_load_b128(r, 0, 0, 0));

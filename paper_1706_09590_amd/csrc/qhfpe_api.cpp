@@ -408,13 +408,15 @@ struct qhfpe_handle {
   // levels of all members
   long long all_levels() const { return mixed ? hmlev[p.batch] : (long long)levels * p.batch; }
   // whether the stages write their outputs non-temporally: the three state
-  // arrays of the step against the MI355X's 256 MB memory-side cache (measured:
-  // 1024-member 128x128 depth-6 FP32 launch 1248 -> 1201 us; at 113 MB, two
-  // 256x256 depth-8 FP64 members, the same stores cost 17%).  Counted are the
-  // levels the stages touch.
+  // arrays of the step well past the MI355X's 256 MB memory-side cache.  Below
+  // that, part of an output that is written through is still there when the next
+  // launch reads it (non-temporal / written through, us per stage; arrays of 100
+  // MB: 256x256x9 five FP64 members 66.4 / 58.1, 128x128x7 54 FP32 members 66.1 /
+  // 61.4; 120 MB: 80.7 / 81.5 with 65 of them; 150 MB: 98.8 / 103 with 82).
+  // Counted are the levels the stages touch.
   bool stream_out() const {
-    constexpr double kMemorySideCacheBytes = 256.0 * 1024 * 1024;
-    return 3.0 * (double)all_levels() * L.level_elems * L.elem > kMemorySideCacheBytes;
+    constexpr double kStreamBytes = 336.0 * 1024 * 1024;
+    return 3.0 * (double)all_levels() * L.level_elems * L.elem > kStreamBytes;
   }
   // one shape for all of the handle's launches, whatever their member groups
   WaveShape shape() const {

@@ -92,6 +92,8 @@ struct WavePlan {
     if (NS == 3 && comp == 2) return kPair22 ? i % 2 : 0;
     return (comp - NS) % 2;
   }
+  // W22 does not share its transform with another component of its column
+  __host__ __device__ static constexpr bool alone(int comp) { return NS == 3 && comp == 2; }
   static_assert(K * L == NP && (L == 16 || L == 32 || L == 64) && 64 % N1 == 0 && N2 % 2 == 0, "wave plan");
 };
 
@@ -730,6 +732,19 @@ __global__ void __launch_bounds__(64 * WPB, OCC) stage_wave_kernel(StageArgs a) 
   // ---- combine, write, level-0 trace partials ----------------------------
   const rsrc_t ro = make_rsrc(at(a.out, at_level), level_bytes);
   const bool want_trace = (a.partials != nullptr) && (n == 0);
+  // Stores.  Left in the L2s as dirty lines, the output would be written back
+  // after the last wave of the launch; written through (kStoreThrough) it
+  // leaves while the launch runs, 4-9% of a mid-sized stage (us: 128 x 64 x 4 FP64,
+  // four members 7.2 -> 6.6; 256 x 256 x 5 three states FP32 17.4 -> 16.0).  That
+  // needs stores of whole lines: a lane's 24 or 32 bytes of FP64 nodes, written
+  // through 16 at a time, cost up to 1.9x.  Where a lane has that much, the
+  // wave therefore turns its columns in LDS so that each store is contiguous
+  // (256 x 256 x 9 FP64 17.4 -> 16.7 one member, 205 -> 204 sixteen; 192 x 192 x 9
+  // 13.45 -> 12.45 and 127 -> 120.7).
+  // Past the memory-side cache (NTS, StageArgs::stream_out) they are
+  // non-temporal: the next launch reads them from HBM anyway.
+  constexpr bool kTurn = ES == 8 && K >= 3;
+  constexpr int kPolicy = NTS ? kStoreNT : kStoreThrough;
 #pragma unroll
   for (int i = 0; i < C; ++i) {
     const int q = q0 + c0l + i;
@@ -739,11 +754,49 @@ __global__ void __launch_bounds__(64 * WPB, OCC) stage_wave_kernel(StageArgs a) 
 #pragma unroll
       for (int j = 0; j < K; ++j)
         o[comp][j] = fma_(coef, loc[i][comp][j] + elem(c0l + i, comp, a0 + j), ky[i][comp][j]);
-      // non-temporal stores (NTS) when the state arrays exceed the
-      // memory-side cache: the output is read back only by the next stage
-      // launch, from HBM anyway, and the stores then drain during the launch
-      // instead of leaving dirty lines for the end-of-launch write-back
-      if (q < nq) buf_store_n<K, NTS ? kStoreNT : 0>(o[comp], ro, qo[i + 3], comp * cbytes);
+      if constexpr (!kTurn) {
+        if (q < nq) buf_store_n<K, kPolicy>(o[comp], ro, qo[i + 3], comp * cbytes);
+      }
+    }
+    if constexpr (kTurn) {
+      // each lane's own nodes back to their places, other nodes out of them
+      constexpr int X = K == 4 ? 2 : 1;  // nodes of a lane's second piece
+      const int x0 = 2 * lig, x1 = 2 * L + X * lig;
+#pragma unroll
+      for (int comp = 0; comp < NC; ++comp) {
+        lds_cx<T>* const z = s + W::transform(c0l + i, comp) * LDP;
+        if (W::alone(comp)) {
+#pragma unroll
+          for (int j = 0; j < K; ++j) elem(c0l + i, comp, a0 + j) = o[comp][j];
+        } else if (W::part(i, comp) == 0) {
+#pragma unroll
+          for (int j = 0; j < K; ++j) z[pad(a0 + j)] = lds_cx<T>{o[comp][j], o[comp + 1][j]};
+        }
+      }
+      wave_lds_sync();
+      const unsigned row = (unsigned)q * (NP * ES);
+#pragma unroll
+      for (int comp = 0; comp < NC; ++comp) {
+        T v0[2][2], v1[2][X];
+        const lds_cx<T>* const z = s + W::transform(c0l + i, comp) * LDP;
+        if (!W::alone(comp) && W::part(i, comp) == 1) continue;  // (went with its real part)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const lds_cx<T> v = W::alone(comp) ? lds_cx<T>{elem(c0l + i, comp, x0 + e), T(0)} : z[pad(x0 + e)];
+          v0[0][e] = v[0], v0[1][e] = v[1];
+        }
+#pragma unroll
+        for (int e = 0; e < X; ++e) {
+          const lds_cx<T> v = W::alone(comp) ? lds_cx<T>{elem(c0l + i, comp, x1 + e), T(0)} : z[pad(x1 + e)];
+          v1[0][e] = v[0], v1[1][e] = v[1];
+        }
+#pragma unroll
+        for (int c = 0; c < (W::alone(comp) ? 1 : 2); ++c)
+          if (q < nq) {
+            buf_store_n<2, kPolicy>(v0[c], ro, row + x0 * ES, (comp + c) * cbytes);
+            buf_store_n<X, kPolicy>(v1[c], ro, row + x1 * ES, (comp + c) * cbytes);
+          }
+      }
     }
     if (want_trace) {
       // one partial per column, its lanes summed by a butterfly
