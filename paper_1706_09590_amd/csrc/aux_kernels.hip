@@ -309,13 +309,13 @@ struct Sample {
   double re, im;
 };
 
-// sum_{s = s0}^{s1 - 1} c_s Im(e^{i om s dt} x_r[s]) for R complex rows x_r of
-// n samples (row stride in samples), added to acc; c_s the trapezoid weights
-template <int R>
-__device__ __forceinline__ void phase_sums(const Sample* __restrict__ x, long long row_stride, long long n,
-                                           long long s0, long long s1, double om, double dt, double (&acc)[R]) {
+// sum_{s = s0}^{s1 - 1} c_s Im(e^{i om s dt} x[s]) of a series of n samples, c_s
+// the trapezoid weights
+__device__ __forceinline__ double phase_sum(const Sample* __restrict__ x, long long n, long long s0, long long s1,
+                                            double om, double dt) {
   const Phase e1 = phase_of(om * dt), ec = phase_of(om * (double)kPhaseChunk * dt);
   Phase base = {1.0, 0.0};
+  double acc = 0.0;
   int k = 0;
   for (long long c = s0; c < s1; c += kPhaseChunk, ++k) {
     base = (k % kPhaseRestart == 0) ? phase_of(om * (double)c * dt) : rotate(base, ec);
@@ -323,26 +323,21 @@ __device__ __forceinline__ void phase_sums(const Sample* __restrict__ x, long lo
     if (c > 0 && c + kPhaseChunk <= s1 && c + kPhaseChunk < n) {
 #pragma unroll
       for (int j = 0; j < kPhaseChunk; ++j) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const Sample v = x[r * row_stride + c + j];
-          acc[r] = fma(e.im, v.re, fma(e.re, v.im, acc[r]));
-        }
+        const Sample v = x[c + j];
+        acc = fma(e.im, v.re, fma(e.re, v.im, acc));
         if (j + 1 < kPhaseChunk) e = rotate(e, e1);
       }
     } else {
       // a chunk with an end of the series, or a partial one
       for (long long s = c; s < min(s1, c + kPhaseChunk); ++s) {
         const double g = (s == 0 || s == n - 1) ? 0.5 : 1.0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const Sample v = x[r * row_stride + s];
-          acc[r] = fma(g * e.im, v.re, fma(g * e.re, v.im, acc[r]));
-        }
+        const Sample v = x[s];
+        acc = fma(g * e.im, v.re, fma(g * e.re, v.im, acc));
         e = rotate(e, e1);
       }
     }
   }
+  return acc;
 }
 
 // samples per segment when n samples are split into at most `segs` segments
@@ -367,9 +362,7 @@ __global__ void __launch_bounds__(kSpectrumThreads)
   const double om = omega[min(w, n_omega - 1)];
   const long long len = segment_length(n, segs);
   const long long s0 = seg * len, s1 = min(n, s0 + len);
-  double acc[1] = {0.0};
-  if (s0 < s1) phase_sums<1>(series, 0, n, s0, s1, om, dt, acc);
-  sh[tid] = acc[0];
+  sh[tid] = s0 < s1 ? phase_sum(series, n, s0, s1, om, dt) : 0.0;
   for (int half = segs / 2; half > 0; half /= 2) {
     __syncthreads();
     if (seg < half) sh[tid] += sh[tid + half * wpb];
@@ -378,77 +371,129 @@ __global__ void __launch_bounds__(kSpectrumThreads)
 }
 
 // im[t1][w3] = Im sum_t3 c dt3 e^{i w3 t3} R3[t1][t3], the part of the t3 sums
-// that the spectrum needs.  A lane holds one frequency and R coherence times,
-// so the phase factors are shared by R rows and the samples are the same for
-// the whole wave (scalar loads); the sixteen waves of a workgroup take a
-// sixteenth of the samples each and meet in LDS.  The launcher takes the
-// largest R that still gives about one workgroup per CU.  64 x 4001 samples
-// at 401 frequencies take 37 us (bound by the latency of the scalar loads:
-// FP64 issue alone is 12 us); with one thread per (t1, frequency) and a
-// sincos per sample the two passes took 1180 us.
+// that the spectrum needs: a contraction over t3, on the FP64 matrix cores
+// (v_mfma_f64_16x16x4: rows t1, columns w3, four samples).  A workgroup holds a
+// 16 x 16 tile; its sixteen waves take a segment of the samples each and meet in
+// LDS, and where the tiles leave CUs idle two workgroups share a tile's samples
+// (partial sums im[0], im[1], which the next kernel adds).  Of eight samples a
+// step, lane (k, column) rotates the factors of samples 2 k, 2 k + 1, which serve
+// sixteen rows; the samples come in blocks of whole 512-byte row pieces and change
+// lanes in LDS (loaded by the lanes that multiply them, 64 cache lines a load, the
+// kernel takes 27 us).  64 x 4001 samples at 401 frequencies take 20 us
+// (7 of them matrix issue); on the vector units with scalar sample loads,
+// bound by those loads, they took 38 us, and with one thread per (t1, frequency)
+// and a sincos per sample the two passes took 1180 us.
 constexpr int kCorrWaves = kSpectrumThreads / 64;
-template <int R>
+constexpr int kCorrTile = 16;
+constexpr int kCorrStep = 8;     // samples per step
+constexpr int kCorrSpan = 32;    // samples per block: one load brings two rows of it
+constexpr int kCorrRestart = 4;  // blocks between sincos: factors at most 16 rotations from one
+constexpr int kCorrRow = kCorrSpan + 1;  // padded LDS row (in samples)
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 __global__ void __launch_bounds__(kSpectrumThreads)
     spectrum_corr_t3_kernel(const Sample* __restrict__ r3, int n1, int n3, double dt3,
-                            const double* __restrict__ w3, int nw3, double* __restrict__ im) {
-  __shared__ double sh[kCorrWaves][R][64];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int seg = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: the samples come through scalar loads
-  const int i0 = blockIdx.y * R;
-  const double om = w3[min((int)blockIdx.x * 64 + lane, nw3 - 1)];
-  const long long len = segment_length(n3, kCorrWaves);
-  const long long s0 = seg * len, s1 = min((long long)n3, s0 + len);
-  double acc[R];
+                            const double* __restrict__ w3, int nw3, int planes, double* __restrict__ im) {
+  typedef double pair __attribute__((ext_vector_type(2)));
+  __shared__ pair slab[kCorrWaves][kCorrTile * kCorrRow];  // per wave: a block of its rows
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, k = lane >> 4;
+  const int row0 = blockIdx.y * kCorrTile, col0 = blockIdx.x * kCorrTile;
+  // (rows and columns past the edges repeat the last one and are not stored)
+  const double om = w3[min(col0 + li, nw3 - 1)];
+  const int segs = kCorrWaves * planes, seg = wid * planes + (int)blockIdx.z;
+  const int per = ((n3 + segs - 1) / segs + kCorrStep - 1) / kCorrStep * kCorrStep;
+  const long long s0 = (long long)seg * per;
+  const int len = (int)max(0ll, min((long long)per, n3 - s0));  // this wave's samples
+  constexpr int kLoads = kCorrTile / 2;
+  const int half = lane / kCorrSpan, ls = lane % kCorrSpan;  // of a load: this lane's row and sample
+  auto load = [&](int at, Sample (&v)[kLoads]) {
+    const long long s = min(s0 + at + ls, (long long)n3 - 1);
 #pragma unroll
-  for (int r = 0; r < R; ++r) acc[r] = 0.0;
-  // (the last workgroup's rows may run past n1: it takes its rows from the end)
-  const int row = min(i0, max(n1 - R, 0));
-  if (s0 < s1) phase_sums<R>(r3 + (long long)row * n3, n3, n3, s0, s1, om, dt3, acc);
+    for (int i = 0; i < kLoads; ++i) v[i] = r3[(long long)min(row0 + 2 * i + half, n1 - 1) * n3 + s];
+  };
+  Sample next[kLoads];
+  if (len > 0) load(0, next);
+  const Phase e1 = phase_of(om * dt3), e8 = phase_of(om * (double)kCorrStep * dt3);
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  Phase e = {1.0, 0.0};
+  for (int at = 0, blk = 0; at < len; at += kCorrSpan, ++blk) {
+    // into LDS with the trapezoid weights of the ends, zero past the segment
+    const bool used = at + ls < len;
+    const double g = (s0 + at + ls == 0 || s0 + at + ls == n3 - 1) ? 0.5 : 1.0;
+    wave_lds_sync();
 #pragma unroll
-  for (int r = 0; r < R; ++r) sh[seg][r][lane] = acc[r];
+    for (int i = 0; i < kLoads; ++i)
+      slab[wid][(2 * i + half) * kCorrRow + ls] = pair{used ? g * next[i].re : 0.0, used ? g * next[i].im : 0.0};
+    wave_lds_sync();
+    load(at + kCorrSpan, next);  // (past the end: the rows' last samples, not used)
+    if (blk % kCorrRestart == 0) e = phase_of(om * (double)(s0 + at + 2 * k) * dt3);
+#pragma unroll
+    for (int t = 0; t < kCorrSpan / kCorrStep; ++t) {
+      const pair* const z = slab[wid] + li * kCorrRow + kCorrStep * t + 2 * k;
+      const pair u = z[0], v = z[1];
+      const Phase f = rotate(e, e1);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(u[0], e.im, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(u[1], e.re, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[0], f.im, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[1], f.re, acc, 0, 0, 0);
+      e = rotate(e, e8);
+    }
+  }
+  // D layout of the FP64 product: row 4 r + lane / 16, column lane % 16
+  double* const mine = reinterpret_cast<double*>(slab[wid]);
+  wave_lds_sync();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) mine[(4 * r + k) * kCorrTile + li] = acc[r];
   __syncthreads();
-  for (int e = tid; e < R * 64; e += kSpectrumThreads) {
-    const int r = e / 64, w = blockIdx.x * 64 + e % 64;
+  if (tid < kCorrTile * kCorrTile) {
     double s = 0.0;
-    for (int k = 0; k < kCorrWaves; ++k) s += sh[k][r][e % 64];
-    if (w < nw3) im[(long long)(row + r) * nw3 + w] = s * dt3;
+#pragma unroll
+    for (int w = 0; w < kCorrWaves; ++w) s += reinterpret_cast<const double*>(slab[w])[tid];
+    const int r = row0 + tid / kCorrTile, w = col0 + tid % kCorrTile;
+    if (r < n1 && w < nw3) im[((long long)blockIdx.z * n1 + r) * nw3 + w] = s * dt3;
   }
 }
 
 // out[w3][w1] = sum_t1 c dt1 2 cos(w1 t1) Im A[t1][w3]: a lane holds one w1 and
 // kCorrRows frequencies w3, which share the cosine; the waves of a workgroup
-// take every kCorrT1Waves-th chunk of kCorrT1Chunk coherence times (whose
-// sums, the same for the whole wave, come through scalar loads issued
-// together) and meet in LDS.  6.9 us for 64 coherence times at 401 x 401
-// frequencies; 21 us as one wave per workgroup with loads one by one.
+// take every kWaves-th chunk of coherence times (whose sums, the same for the
+// whole wave, come through scalar loads issued together: as many as the scalar
+// registers hold) and meet in LDS.  10 us for 64 coherence times at 401 x 401
+// frequencies in two planes (13 with sixteen waves); 21 us for one plane as one
+// wave per workgroup with loads one by one.
 constexpr int kCorrRows = 4;
 constexpr int kCorrT1Waves = 8;
-constexpr int kCorrT1Chunk = 8;
+template <int PLANES>
 __global__ void __launch_bounds__(64 * kCorrT1Waves)
     spectrum_corr_t1_kernel(const double* __restrict__ im, int n1, double dt1, const double* __restrict__ w1,
                             int nw1, int nw3, double* __restrict__ out) {
-  __shared__ double sh[kCorrT1Waves][kCorrRows][64];
+  constexpr int kWaves = kCorrT1Waves, kChunk = 8 / PLANES;
+  __shared__ double sh[kWaves][kCorrRows][64];
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int w0 = blockIdx.y * kCorrRows;
   const double om = w1[min((int)blockIdx.x * 64 + lane, nw1 - 1)];
   const Phase e1 = phase_of(om * dt1);
   double acc[kCorrRows] = {};
-  for (int c = wid * kCorrT1Chunk; c < n1; c += kCorrT1Waves * kCorrT1Chunk) {
-    double x[kCorrT1Chunk][kCorrRows];
+  for (int c = wid * kChunk; c < n1; c += kWaves * kChunk) {
+    double x[kChunk][kCorrRows][PLANES];
 #pragma unroll
-    for (int j = 0; j < kCorrT1Chunk; ++j)
+    for (int j = 0; j < kChunk; ++j)
 #pragma unroll
       for (int r = 0; r < kCorrRows; ++r)
-        x[j][r] = im[(long long)min(c + j, n1 - 1) * nw3 + min(w0 + r, nw3 - 1)];
+#pragma unroll
+        for (int u = 0; u < PLANES; ++u)
+          x[j][r][u] = im[((long long)u * n1 + min(c + j, n1 - 1)) * nw3 + min(w0 + r, nw3 - 1)];
     Phase e = phase_of(om * (double)c * dt1);
 #pragma unroll
-    for (int j = 0; j < kCorrT1Chunk; ++j) {
+    for (int j = 0; j < kChunk; ++j) {
       const int s = c + j;
       if (s < n1) {
         const double g = (s == 0 || s == n1 - 1) ? e.re : 2.0 * e.re;
 #pragma unroll
-        for (int r = 0; r < kCorrRows; ++r) acc[r] = fma(g, x[j][r], acc[r]);
+        for (int r = 0; r < kCorrRows; ++r)
+          acc[r] = fma(g, PLANES == 2 ? x[j][r][0] + x[j][r][PLANES - 1] : x[j][r][0], acc[r]);
       }
       e = rotate(e, e1);
     }
@@ -461,7 +506,7 @@ __global__ void __launch_bounds__(64 * kCorrT1Waves)
   if (r >= kCorrRows || w0 + r >= nw3 || a >= nw1) return;
   double s = 0.0;
 #pragma unroll
-  for (int k = 0; k < kCorrT1Waves; ++k) s += sh[k][r][lane];
+  for (int k = 0; k < kWaves; ++k) s += sh[k][r][lane];
   out[(long long)(w0 + r) * nw1 + a] = s * dt1;
 }
 
@@ -632,21 +677,18 @@ hipError_t launch_spectrum_abs(const double* series, long long n, double dt, con
 
 hipError_t launch_spectrum_corr(const double* r3, int n1, int n3, double dt1, double dt3, const double* w1,
                                 int nw1, const double* w3, int nw3, double* work, double* out, hipStream_t s) {
-  // coherence times per lane: the most that still give about one workgroup
-  // per CU (with 64 x 401: 2 rows, 224 workgroups); at most n1 rows
-  const unsigned bx = (unsigned)((nw3 + 63) / 64);
-  int rows = 8;
-  while (rows > 1 && (rows > n1 || (long long)bx * ((n1 + rows - 1) / rows) < 200)) rows /= 2;
-  const dim3 grid(bx, (unsigned)((n1 + rows - 1) / rows)), block(kSpectrumThreads);
-  const Sample* x = reinterpret_cast<const Sample*>(r3);
-#define F(R) hipLaunchKernelGGL((spectrum_corr_t3_kernel<R>), grid, block, 0, s, x, n1, n3, dt3, w3, nw3, work)
-  if (rows == 8) { F(8); } else if (rows == 4) { F(4); } else if (rows == 2) { F(2); } else { F(1); }
-#undef F
+  // d_work holds two planes; with a workgroup per CU (256 tiles) one is enough
+  const dim3 tiles((nw3 + kCorrTile - 1) / kCorrTile, (n1 + kCorrTile - 1) / kCorrTile);
+  const int planes = (long long)tiles.x * tiles.y < 256 ? 2 : 1;
+  hipLaunchKernelGGL(spectrum_corr_t3_kernel, dim3(tiles.x, tiles.y, planes), dim3(kSpectrumThreads), 0, s,
+                     reinterpret_cast<const Sample*>(r3), n1, n3, dt3, w3, nw3, planes, work);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(spectrum_corr_t1_kernel, dim3((nw1 + 63) / 64, (nw3 + kCorrRows - 1) / kCorrRows),
-                     dim3(64 * kCorrT1Waves), 0, s,
-                     work, n1, dt1, w1, nw1, nw3, out);
+  const dim3 grid((nw1 + 63) / 64, (nw3 + kCorrRows - 1) / kCorrRows), block(64 * kCorrT1Waves);
+  if (planes == 2)
+    hipLaunchKernelGGL(spectrum_corr_t1_kernel<2>, grid, block, 0, s, work, n1, dt1, w1, nw1, nw3, out);
+  else
+    hipLaunchKernelGGL(spectrum_corr_t1_kernel<1>, grid, block, 0, s, work, n1, dt1, w1, nw1, nw3, out);
   return hipGetLastError();
 }
 

@@ -60,3 +60,34 @@ def test_correlation_sums(n1, n3, nw1, nw3):
     ref = 2.0 * d1 * (A * weights(n1)) @ np.cos(w1[:, None] * np.arange(n1) * d1).T
     scale = 2.0 * d1 * d3 * np.abs(x).sum()
     assert np.max(np.abs(got - ref)) <= scale * EPS * (4 * (22.0 * n3 * d3 + 20.0 * n1 * d1) + 2 * 64)
+
+
+# edges of the 16 x 16 tiles and of the eight-sample steps, one tile to more
+# than 256 of them; rows on an 8-byte boundary
+@pytest.mark.parametrize("n1,n3,nw3", [(2, 7, 1), (15, 8, 16), (16, 9, 17), (17, 255, 15), (31, 256, 33),
+                                       (32, 257, 31), (16, 1023, 16), (48, 1025, 100), (130, 64, 530)])
+def test_correlation_tiles(n1, n3, nw3):
+    rng = np.random.default_rng(n1 + n3)
+    x = rng.standard_normal((n1, n3)) + 1j * rng.standard_normal((n1, n3))
+    d1, d3, w1, w3 = 0.05, 0.01, np.array([0.0, 3.0]), np.linspace(0.0, 22.0, nw3)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    om1, om3 = dev(w1), dev(w3)
+    s = torch.cuda.current_stream().cuda_stream
+
+    def spectrum(x):
+        buf = torch.zeros(2 * n1 * n3 + 1, dtype=torch.float64, device="cuda")
+        buf[1:] = dev(x.ravel().view(np.float64))
+        work = torch.full((2 * n1 * nw3,), float("nan"), dtype=torch.float64, device="cuda")
+        out = torch.empty((nw3, 2), dtype=torch.float64, device="cuda")
+        rc = qhfpe.lib().qhfpe_spectrum_corr(buf[1:].data_ptr(), n1, n3, d1, d3, om1.data_ptr(), 2, om3.data_ptr(),
+                                             nw3, work.data_ptr(), out.data_ptr(), s)
+        assert rc == qhfpe.OK
+        return out.cpu().numpy()
+
+    ph = w3[:, None] * np.arange(n3) * d3
+    A = d3 * ((np.sin(ph) * weights(n3)) @ x.real.T + (np.cos(ph) * weights(n3)) @ x.imag.T)
+    ref = 2.0 * d1 * (A * weights(n1)) @ np.cos(w1[:, None] * np.arange(n1) * d1).T
+    scale = 2.0 * d1 * d3 * np.abs(x).sum()
+    got = spectrum(x)
+    assert np.max(np.abs(got - ref)) <= scale * EPS * (4 * (22.0 * n3 * d3 + 3.0 * n1 * d1) + 2 * 64)
+    assert np.array_equal(got, spectrum(x))
