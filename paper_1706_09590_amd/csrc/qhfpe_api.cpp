@@ -374,6 +374,19 @@ struct qhfpe_handle {
     return std::min(want, p.batch);
   }
 
+  // Groups of one step call.  The default rule's groups overlap launches, but each
+  // costs the host 3.2 us per stage to enqueue, so where one launch of all members
+  // is over sooner it is one (us per stage, one / two groups: 48x48x4 FP32 four
+  // members, 0.6 MB of state, 4.9 / 6.3; 128x128x7 FP32 three, 5.5 MB, 8.6 / 9.4;
+  // 96x96x7 FP64 three, 6.2 MB, 8.3 / 8.8; 128x128x7 FP32 four, 7.3 MB, 9.35 /
+  // 9.3; 96x96x7 FP32 eight, 8.3 MB, 10.1 / 8.6; 256x256x9 FP64 two, 75 MB, 30 /
+  // 21.9).  A recorded step is not enqueued launch by launch and keeps the groups.
+  int step_groups(bool recorded) const {
+    constexpr double kLaunchBoundBytes = 7.0e6;
+    const bool small = (double)all_levels() * L.level_elems * L.elem < kLaunchBoundBytes;
+    return groups_req == 0 && small && !recorded ? 1 : groups();
+  }
+
   hipError_t make_groups(int n) {
     if (!gfork) {
       hipError_t e = hipEventCreateWithFlags(&gfork, hipEventDisableTiming);
@@ -1019,16 +1032,18 @@ int step_enqueue(qhfpe_t* h, int64_t nsteps, int32_t stride, double* d_resp) {
   StageArgs s4 = h->stage_args(h->va(), h->vb(), h->y(), kA2 * dt);
   // member groups: group g holds members first[g] .. first[g + 1] - 1 and
   // runs on its own stream between a fork and a join on the handle's stream
-  int G = nsteps > 0 ? h->groups() : 1;
+  const bool recorded = capturing(h);
+  int G = nsteps > 0 ? h->step_groups(recorded) : 1;
   // no stream is created while the handle's stream records a graph; the
   // results do not depend on the grouping
-  if (G > h->groups_made && capturing(h)) G = 1;
+  if (G > h->groups_made && recorded) G = 1;
+  // (a later recording may want them)
+  if (nsteps > 0 && !recorded && h->groups() > 1) HIP_TRY(h->make_groups(h->groups()));
   int first[kMaxGroups + 1];
   for (int g = 0; g <= G; ++g) first[g] = (int)((long long)g * h->p.batch / G);
   hipStream_t gs[kMaxGroups];
   StageArgs g1[kMaxGroups], g2[kMaxGroups], g3[kMaxGroups];
   if (G > 1) {
-    HIP_TRY(h->make_groups(G));
     HIP_TRY(hipEventRecord(h->gfork, h->stream));
     for (int g = 0; g < G; ++g) {
       gs[g] = h->gstream[g];

@@ -182,3 +182,37 @@ def test_workgroup_sizes_agree_bitwise(precision):
     got = run(d, 10, precision, 1, 2, 12, 3)
     for a, b in zip(got, ref):
         assert np.array_equal(a, b), np.max(np.abs(a - b))
+
+
+@pytest.mark.parametrize("np_,nq,depth,batch", [(48, 24, 1, 2), (64, 40, 3, 3), (128, 128, 6, 3), (128, 128, 6, 4),
+                                                (96, 64, 4, 16)])
+def test_default_launches_agree_with_any_grouping(np_, nq, depth, batch):
+    """The default's eager steps (one launch per stage below 7 MB of state, which
+    lies between three and four members of 128 x 128 x 7, else member groups)
+    and its recorded ones equal every explicit grouping."""
+    d = model(nq=nq, np_=np_, depth=depth)
+    s = torch.cuda.Stream()
+    want = None
+    for groups, recorded in ((0, False), (0, True), (1, False), (2, False)):
+        P = qhfpe.Propagator(d, batch=batch, precision="fp32", stream=s)
+        for m in range(batch):
+            P.set_member_bath(m, *BATHS[m % len(BATHS)])
+        P.set_streams(groups)
+        with torch.cuda.stream(s):
+            P.init_thermal(1.0)
+            P.apply_dipole()
+        out = torch.empty((batch, 4), dtype=torch.complex128, device="cuda")
+        P.step(2, 1)
+        if recorded:
+            g = qhfpe.Graph(s)
+            with g, torch.cuda.stream(s):
+                P.step(6, 2, out=out, asynchronous=True)
+            g.launch()
+        else:
+            with torch.cuda.stream(s):
+                P.step(6, 2, out=out, asynchronous=True)
+        P.status()
+        got = out.cpu().numpy(), P.get_state().cpu().numpy()
+        P.close()
+        want = want or got
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), (groups, recorded)
