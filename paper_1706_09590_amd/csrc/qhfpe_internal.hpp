@@ -87,8 +87,10 @@ inline int wave_columns_of(int np, int c) { return wave_groups(np) * c; }
 //   waves 6.2 / 6.5 / 8.1, 10240 waves 14.3 / 10.9 / 10.2; 256 FP64, 192 waves
 //   9.0 / 10.1, 2304 waves 21.2 / 18.2; 96 FP64 (two lane groups), 1344 waves
 //   10.3 / 11.4, 5376 waves 23.5 / 19.8 / 32.7.
-//   three states: 128 FP32, 14336 waves 49.5 / 40.6; 256 FP32, 9216 waves
-//   55.6 with one (two would leave LDS for six waves a CU).
+//   three states: 128 FP32, 7544 waves 33.8 / 34.2, 13530 waves 49.2 / 46.9;
+//   128 FP64, 8036 waves 48.5 / 53.3, 12300 waves 86.5 / 86.2; 64 FP64, 11520
+//   waves 41.8 / 36.6; 256 FP32, 9216 waves 55.6 with one (two would leave LDS
+//   for six waves a CU).
 // Components in flight: with SIMDs to spare a one-column wave issues two (three
 // for nine components; in FP32 all four of two states: 64 x 64 5.2 against
 // 5.3 us); otherwise the staggered schedule, except FP32 at 256, whose second
@@ -100,7 +102,7 @@ inline WaveShape wave_shape(int elem_bytes, int ns, int np, bool qcoup, long lon
   const bool f32 = elem_bytes == 4;
   if (ns == 3) {
     const bool pairs = np == 128 || np == 64;  // two columns fit
-    if (pairs && (stream || waves >= 7000)) return {2, kStaggered, 2};
+    if (pairs && (stream || waves >= (np == 64 ? 7000 : 11000))) return {2, kStaggered, 2};
     if ((f32 || pairs) && !stream && waves <= 2000) return {1, 3, 1};
     return {1, kStaggered, 2};
   }
