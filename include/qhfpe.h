@@ -156,8 +156,9 @@ int qhfpe_set_member_depth(qhfpe_t* h, int32_t member, int32_t depth);
  * otherwise it is q-dependent and enters the r-space multiply, where
  * -(i/hbar) [U_jl(q + r/2) W_lk - W_jl U_lk(q - r/2)] mixes the diagonal and
  * coherence transforms of a column.  Two variants implement it: the
- * two-state wave variant (tile 1, np = 128 or 256) and the workgroup
- * variant with 2 cells per thread (tile 2, every np, two and three states).
+ * two-state wave variant (tile 1, np = 128 or 256; at np = 32, 48, 64, 96 and
+ * 192 it computes tile 2) and the workgroup variant with 2 cells per thread
+ * (tile 2, every other np, two and three states).
  * The handle moves to one of them if its variant has no such path, and
  * qhfpe_set_tile with another variant fails until a potential with
  * constant couplings is set again.  Synchronous.
