@@ -151,7 +151,7 @@ struct StageArgs {
   const void* v;         // stage input, packed [B][N+1][nc][nq][np]
   const void* y;         // RK4 base state (nullptr: treated as zero)
   void* out;             // y + coef * L v
-  double* partials;      // [B][kRespSlots][ntiles] level-0 trace partials, or nullptr
+  double* partials;      // [B][kRespSlots][npartials] level-0 trace partials, or nullptr
   const void* twiddle2;  // [n1][n2+1] complex exp(+2 pi i (n2 k1 mod np)/np), state precision
   const void* dtab;      // [ns][nq][np]: (U_j(q+r/2) - U_j(q-r/2)) / (2 hbar np), 0 at Nyquist
   const void* gtab;      // [npair][nq][np]: (U_j(q+r/2) - U_k(q-r/2)) / (hbar np), j < k
@@ -177,8 +177,8 @@ struct StageArgs {
   int ntiles;
   int batch;
   int nblocks_padded;       // grid size: ntiles * (depth+1) * batch rounded up to a multiple of 8
-  int stream_out;           // wave variant: 1 = non-temporal output stores (the state exceeds the
-                            // memory-side cache)
+  int stream_out;           // wave variant: 1 = non-temporal output stores (the state arrays are well
+                            // past the memory-side cache)
   WaveShape shape;          // wave variant
   int npartials;            // trace partials per member and slot (wave variant: one per column)
   FixedDiv by_levels, by_tiles;  // division by depth + 1 and by ntiles

@@ -30,14 +30,13 @@
 // What bounds it: a small launch (each wave on a SIMD of its own) by one
 // wave's chain of launch, loads and FFT rounds, a large one by how well the
 // waves' load and transform phases overlap (no unit is saturated: 1024 members
-// of 128 x 128 x 7 levels in FP32 take 1.22 ms, of which VALU issue is 0.7 and
+// of 128 x 128 x 7 levels in FP32 take 1.18 ms, of which VALU issue is 0.7 and
 // the bytes at the copy rate 0.85).  wave_shape (qhfpe_internal.hpp) holds the
 // rule and its measurements.  Against one fixed shape at 128 and 256 and the
-// workgroup variant elsewhere (us per stage launch, FP64 unless said): 48 x 48
-// x 4 levels, one member 11.4 -> 5.8; 128 x 128 x 7 one member 10.9 -> 7.7;
-// 96 x 96 x 7 four members 13.0 -> 10.3; 192 x 192 x 9 sixteen members 171 -> 125;
-// three states 64 x 64 x 5 sixteen members 35.7 -> 18.0; 256 x 256 x 9 two
-// members 25.5 -> 22.8.
+// workgroup variant elsewhere (us per stage, FP64): 48 x 48 x 4 levels, one
+// member 11.4 -> 5.5; 128 x 128 x 7 one member 10.9 -> 6.5; 96 x 96 x 7 four members
+// 13.0 -> 10.5; 192 x 192 x 9 sixteen members 171 -> 120; three states 64 x 64 x 3
+// sixty members 82.5 -> 36.6; 256 x 256 x 9 two members 25.5 -> 21.9.
 //
 // Every column is computed by the same operations in the same order whatever
 // C, PF and the workgroup shape are (contraction is off, the fused
@@ -167,7 +166,7 @@ __device__ __forceinline__ void dft16_four_lanes(int lane, int items, int stride
 // levels after c's.  OCC: waves per SIMD the register allocation
 // aims at.  QC: q-dependent diabatic coupling
 // U_01(q), applied in the r-space multiply.  NTS: non-temporal output stores
-// (StageArgs::stream_out).  WPB: waves per workgroup (StageArgs::wpb).  MIX:
+// (StageArgs::stream_out).  WPB: waves per workgroup (StageArgs::shape).  MIX:
 // members of their own depths (StageArgs::mlev).
 template <typename T, int NS, int NP, int C, int PF, int OCC, bool QC, bool NTS, int WPB, bool MIX>
 __global__ void __launch_bounds__(64 * WPB, OCC) stage_wave_kernel(StageArgs a) {
