@@ -161,7 +161,9 @@ int qhfpe_set_member_depth(qhfpe_t* h, int32_t member, int32_t depth);
  * (tile 2, every other np, two and three states).
  * The handle moves to one of them if its variant has no such path, and
  * qhfpe_set_tile with another variant fails until a potential with
- * constant couplings is set again.  Synchronous.
+ * constant couplings is set again, which returns the handle to the variant
+ * it had before (or keeps one chosen since with qhfpe_set_tile,
+ * qhfpe_autotune or qhfpe_set_closure).  Synchronous.
  * Errors: QHFPE_EINVAL (fn NULL, a non-finite value); on error the handle
  * keeps its previous surfaces. */
 typedef double (*qhfpe_potential_fn)(int32_t j, int32_t l, double x, void* ctx);

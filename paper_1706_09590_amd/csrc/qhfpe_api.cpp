@@ -83,8 +83,10 @@ int validate(const qhfpe_params* p) {
         return fail(QHFPE_EINVAL, "mu must be finite and symmetric");
     }
   const long double elems = (long double)p->batch * (p->depth + 1) * ns * ns * p->nq * p->np;
-  // (the cap also keeps a stage grid's count of q tiles x levels x members,
-  // about elems / (512 ns^2) plus levels x members, far below 2^31)
+  // (the cap also keeps a stage grid's count of q tiles x levels x members below
+  // 2^31: a tile of a launch of many waves holds at least 128 cells, four columns
+  // of 32 points, so at most elems / (128 ns^2) = 7.8e8, plus levels x members,
+  // at most 4.3e6)
   if (elems > 4.0e11L) return fail(QHFPE_EINVAL, "state too large");
   // one hierarchy level of one member is addressed with 32-bit byte offsets
   const long double level_bytes = (long double)ns * ns * p->nq * p->np * 8.0L;
@@ -327,6 +329,9 @@ struct qhfpe_handle {
   int phase = 0;
   int ns = 0, nc = 0, levels = 0;
   int cpt = 4;  // stage tile variant (cells per thread along q)
+  // the variant that a q-dependent coupling moved the handle from, taken again
+  // when the couplings are constant (0: none, or the caller chose one since)
+  int cpt_before_qc = 0;
   // off-diagonal couplings: constant (coup, applied pointwise) or
   // q-dependent (qcoup: the r-space multiply of the wave variant)
   double coup[QHFPE_MAX_STATES][QHFPE_MAX_STATES] = {};
@@ -679,7 +684,13 @@ int install_surfaces(qhfpe_t* h, const Surfaces& U) {
   for (int j = 0; j < QHFPE_MAX_STATES; ++j)
     for (int l = 0; l < QHFPE_MAX_STATES; ++l) h->coup[j][l] = (j < h->ns && l < h->ns) ? coup[j][l] : 0.0;
   h->qcoup = coup_const ? 0 : 1;
-  if (h->qcoup && !h->qc_variant(h->cpt)) h->cpt = wave_supported(h->ns, h->p.np) ? kTileWave : kQcCpt;
+  if (h->qcoup && !h->qc_variant(h->cpt)) {
+    h->cpt_before_qc = h->cpt;
+    h->cpt = wave_supported(h->ns, h->p.np) ? kTileWave : kQcCpt;
+  } else if (!h->qcoup && h->cpt_before_qc) {
+    h->cpt = h->cpt_before_qc;
+    h->cpt_before_qc = 0;
+  }
   return QHFPE_OK;
 }
 
@@ -862,6 +873,7 @@ int qhfpe_set_tile(qhfpe_t* h, int32_t cells_per_thread) {
   if (h->closure_out && c != kTileWave)
     return fail(QHFPE_EUNSUPPORTED, "a learned closure needs the wave variant (tile 1)");
   h->cpt = c;
+  h->cpt_before_qc = 0;
   return QHFPE_OK;
 }
 
@@ -905,6 +917,7 @@ int qhfpe_autotune(qhfpe_t* h, int32_t reps, int32_t* h_chosen) {
   (void)hipEventDestroy(e0);  // the events are scratch; a release failure changes no result
   (void)hipEventDestroy(e1);
   h->cpt = best;
+  if (rc == QHFPE_OK) h->cpt_before_qc = 0;
   if (rc == QHFPE_OK && h_chosen) *h_chosen = best;
   return rc;
 }
@@ -1299,6 +1312,7 @@ int qhfpe_set_closure(qhfpe_t* h, const float* d_kernel, void* d_buffer, size_t 
   h->closure_wb = wb;
   h->closure_out = static_cast<char*>(d_buffer) + align_up((size_t)kClosureWeightElems * sizeof(unsigned short));
   h->cpt = kTileWave;
+  h->cpt_before_qc = 0;
   return QHFPE_OK;
 }
 

@@ -1,0 +1,101 @@
+"""A handle whose potential changes: the stage variant and the multiplier
+tables follow the potential that is installed, whatever was installed
+before, bit for bit."""
+
+import numpy as np
+import pytest
+
+from paper_1706_09590_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+if not torch.cuda.is_available():  # pragma: no cover - CPU container
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_1706_09590_amd import qhfpe  # noqa: E402
+
+
+def constant(j, l, x):
+    return 0.5 * (x - 0.3 * j) ** 2 + 3.0 * j if j == l else 0.2
+
+
+def q_dependent(j, l, x):
+    return 0.5 * x * x + 2.0 * j if j == l else 0.3 * np.exp(-0.2 * (x - 0.1 * (j + l)) ** 2)
+
+
+def run(ns, np_, precision, setup):
+    d = inputs.model_dict(inputs.SMALL_ABSORPTION["model"], n_states=ns, nq=18, np=np_, depth=2, dt=0.001)
+    if ns == 3:
+        d.update(poly=inputs.three_state_surfaces(0.3, 0.2), mu=[[0, 1, 0], [1, 0, 0.4], [0, 0.4, 0]])
+    P = qhfpe.Propagator(d, batch=1, precision=precision)
+    try:
+        setup(P)
+        P.init_thermal(1.0)
+        P.apply_dipole()
+        tr = P.step(6, 2).cpu().numpy()
+        return tr, P.get_state().cpu().numpy()
+    finally:
+        P.close()
+
+
+def same(a, b):
+    return all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("ns,np_", [(2, 24), (2, 48), (2, 64), (2, 96), (2, 128), (2, 192), (2, 256), (3, 64), (3, 96),
+                                    (3, 128), (3, 256)])
+def test_a_constant_coupling_returns_to_the_first_variant(ns, np_, precision):
+    want = run(ns, np_, precision, lambda P: P.set_potential(constant))
+
+    def there_and_back(P):
+        P.set_potential(q_dependent)
+        P.set_potential(constant)
+
+    def two_there_and_back(P):
+        P.set_potential(q_dependent)
+        P.set_potential(lambda j, l, x: q_dependent(j, l, x + 0.2))
+        P.set_potential(constant)
+
+    assert same(run(ns, np_, precision, there_and_back), want)
+    assert same(run(ns, np_, precision, two_there_and_back), want)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("ns,np_", [(2, 24), (2, 64), (2, 96), (2, 128), (2, 256), (3, 64), (3, 128)])
+def test_a_q_dependent_coupling_after_a_constant_one(ns, np_, precision):
+    want = run(ns, np_, precision, lambda P: P.set_potential(q_dependent))
+
+    def through_constant(P):
+        P.set_potential(lambda j, l, x: q_dependent(j, l, x + 0.2))
+        P.set_potential(constant)
+        P.set_potential(q_dependent)
+
+    assert same(run(ns, np_, precision, through_constant), want)
+
+
+@pytest.mark.parametrize("np_", [64, 128])
+def test_the_callers_variant_is_kept(np_):
+    """Chosen before a q-dependent coupling: back after it.  Chosen under it:
+    it stays."""
+    def chosen(tile):
+        def setup(P):
+            P.set_potential(constant)
+            P.set_tile(tile)
+        return setup
+
+    def before(P):
+        P.set_tile(8)
+        P.set_potential(q_dependent)
+        P.set_potential(constant)
+
+    def under(P):
+        P.set_tile(8)
+        P.set_potential(q_dependent)
+        P.set_tile(2)
+        P.set_potential(constant)
+
+    want8, want2 = run(2, np_, "fp32", chosen(8)), run(2, np_, "fp32", chosen(2))
+    assert not same(want8, run(2, np_, "fp32", chosen(0)))  # (the variants differ by rounding)
+    assert same(run(2, np_, "fp32", before), want8)
+    assert same(run(2, np_, "fp32", under), want2)
