@@ -207,7 +207,7 @@ __global__ void __launch_bounds__(kBlock)
 template <typename T, int NS>
 __global__ void __launch_bounds__(kBlock)
     trace_kernel(GridDesc g, const T* __restrict__ packed, DipoleMu mu, int tq, int ntiles,
-                 double* __restrict__ partials, int slot) {
+                 double* __restrict__ partials) {
   const int lane = threadIdx.x & 63;
   const int tile = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6), b = blockIdx.y;
   if (tile >= ntiles) return;
@@ -225,19 +225,19 @@ __global__ void __launch_bounds__(kBlock)
         tr += 2.0 * mu.m[j][k] * (double)p[Packing<NS>::re(j, k) * g.comp_stride + ia];
   }
   for (int off = 32; off > 0; off >>= 1) tr += __shfl_xor(tr, off, 64);
-  if (lane == 0) partials[((long long)b * kRespSlots + slot) * ntiles + tile] = tr;
+  if (lane == 0) partials[(long long)b * ntiles + tile] = tr;
 }
 
 // One wave per response sample: its lanes sum the partials (lane by lane in
 // order, then a butterfly).
 __global__ void __launch_bounds__(kBlock)
-    finalize_kernel(int ntiles, int nslots, const double* __restrict__ partials, double scale, int phase,
-                    double* __restrict__ resp, long long resp_stride, long long resp_offset, int* flag) {
+    finalize_kernel(int ntiles, int nslots, const double* __restrict__ partials, long long slot_stride, double scale,
+                    int phase, double* __restrict__ resp, long long resp_stride, long long resp_offset, int* flag) {
   const int lane = threadIdx.x & 63;
   const int j = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   const int b = blockIdx.y;
   if (j >= nslots) return;
-  const double* p = partials + ((long long)b * kRespSlots + j) * ntiles;
+  const double* p = partials + j * slot_stride + (long long)b * ntiles;
   double s = 0.0;
   for (int t = lane; t < ntiles; t += 64) s += p[t];
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
@@ -600,23 +600,24 @@ hipError_t launch_thermal(const GridDesc& g, void* packed, double q0, double dq,
 }
 
 hipError_t launch_trace_partials(const GridDesc& g, const void* packed, const double mu[3][3], int tq,
-                                 int ntiles, double* partials, int slot, hipStream_t s) {
+                                 int ntiles, double* partials, hipStream_t s) {
   DipoleMu m;
   for (int j = 0; j < 3; ++j)
     for (int k = 0; k < 3; ++k) m.m[j][k] = mu[j][k];
   const dim3 grid((ntiles + kBlock / 64 - 1) / (kBlock / 64), g.batch);
 #define F(T, NS) hipLaunchKernelGGL((trace_kernel<T, NS>), grid, dim3(kBlock), 0, s, g, \
-                                    static_cast<const T*>(packed), m, tq, ntiles, partials, slot)
+                                    static_cast<const T*>(packed), m, tq, ntiles, partials)
   QHFPE_DISPATCH(g, F);
 #undef F
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(int batch, int ntiles, int nslots, const double* partials, double scale, int phase,
-                           double* resp, long long resp_stride, long long resp_offset, int* flag, hipStream_t s) {
+hipError_t launch_finalize(int batch, int ntiles, int nslots, const double* partials, long long slot_stride,
+                           double scale, int phase, double* resp, long long resp_stride, long long resp_offset, int* flag,
+                           hipStream_t s) {
   const dim3 grid((nslots + kBlock / 64 - 1) / (kBlock / 64), batch);
-  hipLaunchKernelGGL(finalize_kernel, grid, dim3(kBlock), 0, s, ntiles, nslots, partials, scale, phase, resp,
-                     resp_stride, resp_offset, flag);
+  hipLaunchKernelGGL(finalize_kernel, grid, dim3(kBlock), 0, s, ntiles, nslots, partials, slot_stride, scale,
+                     phase, resp, resp_stride, resp_offset, flag);
   return hipGetLastError();
 }
 

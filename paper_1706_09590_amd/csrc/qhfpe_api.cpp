@@ -48,7 +48,8 @@ struct Layout {
   int n1 = 0, n2 = 0;
   size_t total = 0;
   size_t red_count = 0;
-  int max_tiles = 0;  // trace partials per member and slot: one per tile of the narrowest workgroup
+  int slots = 0;      // response samples buffered between finalisations
+  int max_tiles = 0;  // trace partials per member and sample: one per tile of the narrowest workgroup
                       // variant, or one per column where the wave variant exists
 };
 
@@ -123,7 +124,9 @@ Layout make_layout(const qhfpe_params* p) {
   L.off_vb = off;
   off += L.state_bytes;
   L.off_partials = off;
-  off += align_up((size_t)p->batch * kRespSlots * L.max_tiles * sizeof(double));
+  const size_t sample_bytes = (size_t)p->batch * L.max_tiles * sizeof(double);
+  L.slots = (int)std::min<size_t>(kMaxRespSlots, std::max<size_t>(kMinRespSlots, kPartialBytes / sample_bytes));
+  off += align_up(L.slots * sample_bytes);
   L.off_red = off;
   off += align_up(L.red_count * sizeof(double));
   L.n1 = pl->n1;
@@ -444,10 +447,11 @@ struct qhfpe_handle {
   // q columns per unit of a stage launch
   int tq() const { return wave() ? wave_columns_of(p.np, shape().c) : plan_groups(p.np) * cpt; }
   int ntiles() const { return (p.nq + tq() - 1) / tq(); }
-  // columns per trace partial, partials per member and slot
+  // columns per trace partial, partials per member and sample, of all members
   int partial_columns() const { return wave() ? 1 : tq(); }
   int npartials() const { return (p.nq + partial_columns() - 1) / partial_columns(); }
-  // the trace partials hold L.max_tiles per member and slot: a variant with
+  long long slot_stride() const { return (long long)p.batch * npartials(); }
+  // the trace partials hold L.max_tiles per member and sample: a variant with
   // more would index past them
   bool tile_fits(int code) const {
     return wave_exists(p.np) || (p.nq + plan_groups(p.np) * code - 1) / (plan_groups(p.np) * code) <= L.max_tiles;
@@ -505,7 +509,6 @@ struct qhfpe_handle {
     a.bath = bath();
     a.psym = psym();
     a.closure = closure_out;
-    a.slot = 0;
     a.nq = p.nq;
     a.depth = p.depth;
     a.ntiles = ntiles();
@@ -554,7 +557,7 @@ struct qhfpe_handle {
     a.out = static_cast<char*>(a.out) + off;
     if (a.closure) a.closure = static_cast<const char*>(a.closure) + (size_t)first * L.level_elems * L.elem;
     a.bath += (long long)kBathStride * first;
-    if (a.partials) a.partials += (long long)first * kRespSlots * a.npartials;
+    if (a.partials) a.partials += (long long)first * a.npartials;
     a.batch = count;
     if (a.mlev) a.mfirst = first;
     a.nblocks_padded = padded_blocks(first, count);
@@ -604,24 +607,23 @@ int check_handle(const qhfpe_t* h) {
 
 // partial sums of the level-0 trace of y into slot, then (optionally) finalise
 int trace_into(qhfpe_t* h, int slot) {
-  HIP_TRY(launch_trace_partials(h->grid(), h->y(), h->p.mu, h->partial_columns(), h->npartials(), h->partials(), slot,
-                                h->stream));
+  HIP_TRY(launch_trace_partials(h->grid(), h->y(), h->p.mu, h->partial_columns(), h->npartials(),
+                                h->partials() + slot * h->slot_stride(), h->stream));
   return QHFPE_OK;
 }
 
 int finalize(qhfpe_t* h, int nslots, double* resp, long long resp_stride, long long offset) {
-  HIP_TRY(launch_finalize(h->p.batch, h->npartials(), nslots, h->partials(), h->dq * h->dp, h->phase, resp,
-                          resp_stride, offset, h->flag(), h->stream));
+  HIP_TRY(launch_finalize(h->p.batch, h->npartials(), nslots, h->partials(), h->slot_stride(), h->dq * h->dp, h->phase,
+                          resp, resp_stride, offset, h->flag(), h->stream));
   return QHFPE_OK;
 }
 
 // finalize for members first .. first + count - 1 on stream s
 int finalize_members(qhfpe_t* h, int first, int count, int nslots, double* resp, long long resp_stride,
                      long long offset, hipStream_t s) {
-  HIP_TRY(launch_finalize(count, h->npartials(), nslots,
-                          h->partials() + (long long)first * kRespSlots * h->npartials(),
-                          h->dq * h->dp, h->phase, resp ? resp + (long long)first * resp_stride : nullptr,
-                          resp_stride, offset, h->flag(), s));
+  HIP_TRY(launch_finalize(count, h->npartials(), nslots, h->partials() + (long long)first * h->npartials(),
+                          h->slot_stride(), h->dq * h->dp, h->phase,
+                          resp ? resp + (long long)first * resp_stride : nullptr, resp_stride, offset, h->flag(), s));
   return QHFPE_OK;
 }
 
@@ -1074,15 +1076,14 @@ int step_enqueue(qhfpe_t* h, int64_t nsteps, int32_t stride, double* d_resp) {
   auto run = [&]() -> int {
     for (int64_t s = 1; s <= nsteps; ++s) {
       const bool sample = d_resp && (s % stride == 0);
-      s4.partials = sample ? h->partials() : nullptr;
-      s4.slot = slot;
+      s4.partials = sample ? h->partials() + slot * h->slot_stride() : nullptr;
       for (int g = 0; g < G; ++g) {
         HIP_TRY(h->launch_on(g1[g], gs[g]));
         HIP_TRY(h->launch_on(g2[g], gs[g]));
         HIP_TRY(h->launch_on(g3[g], gs[g]));
         HIP_TRY(h->launch_on(G > 1 ? h->member_slice(s4, first[g], first[g + 1] - first[g]) : s4, gs[g]));
       }
-      if (sample && ++slot == kRespSlots) {
+      if (sample && ++slot == h->L.slots) {
         for (int g = 0; g < G; ++g)
           if (int rc = finalize_members(h, first[g], first[g + 1] - first[g], slot, d_resp, nsamples * 2, base,
                                         gs[g]))

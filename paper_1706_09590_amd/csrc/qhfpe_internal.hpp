@@ -12,7 +12,12 @@
 namespace qhfpe {
 
 constexpr int kBlock = 256;        // threads per workgroup of every grid kernel
-constexpr int kRespSlots = 256;    // response samples buffered between finalisations
+// Response samples buffered between finalisations: as many as kPartialBytes of
+// trace partials hold, but at least kMinRespSlots (a batch of many members then
+// holds at most 128 bytes of partials per column and member, 8% of the smallest
+// state) and at most kMaxRespSlots.
+constexpr int kMaxRespSlots = 256, kMinRespSlots = 16;
+constexpr size_t kPartialBytes = size_t(2) << 20;
 constexpr int kBathStride = 8;     // doubles per member in the bath table
 
 // Two-pass FFT plan along p (np = n1 * n2, n1 even) for every supported np.
@@ -151,7 +156,7 @@ struct StageArgs {
   const void* v;         // stage input, packed [B][N+1][nc][nq][np]
   const void* y;         // RK4 base state (nullptr: treated as zero)
   void* out;             // y + coef * L v
-  double* partials;      // [B][kRespSlots][npartials] level-0 trace partials, or nullptr
+  double* partials;      // [B][npartials] level-0 trace partials of one sample, or nullptr
   const void* twiddle2;  // [n1][n2+1] complex exp(+2 pi i (n2 k1 mod np)/np), state precision
   const void* dtab;      // [ns][nq][np]: (U_j(q+r/2) - U_j(q-r/2)) / (2 hbar np), 0 at Nyquist
   const void* gtab;      // [npair][nq][np]: (U_j(q+r/2) - U_k(q-r/2)) / (hbar np), j < k
@@ -170,7 +175,6 @@ struct StageArgs {
   const int* mlev;
   const int* lev_member;
   int mfirst;
-  int slot;
   int qcoup;  // 1: q-dependent coupling through the r-space multiply (wave variant, two states)
   int nq;
   int depth;
@@ -180,7 +184,7 @@ struct StageArgs {
   int stream_out;           // wave variant: 1 = non-temporal output stores (the state arrays are well
                             // past the memory-side cache)
   WaveShape shape;          // wave variant
-  int npartials;            // trace partials per member and slot (wave variant: one per column)
+  int npartials;            // trace partials per member (wave variant: one per column)
   FixedDiv by_levels, by_tiles;  // division by depth + 1 and by ntiles
   double inv_60dq, inv_12dp;     // 1 / (60 dq), 1 / (12 dp)
   long long member_stride;  // elements per member
@@ -273,8 +277,9 @@ hipError_t launch_thermal(const GridDesc& g, void* packed, double q0, double dq,
                           double dp, const double* bath, double omega, double mass, double hbar,
                           const double* noise, hipStream_t s);
 hipError_t launch_trace_partials(const GridDesc& g, const void* packed, const double mu[3][3],
-                                 int tq, int ntiles, double* partials, int slot, hipStream_t s);
-hipError_t launch_finalize(int batch, int ntiles, int nslots, const double* partials,
+                                 int tq, int ntiles, double* partials, hipStream_t s);
+// partials of member b's sample j: partials + j slot_stride + b ntiles
+hipError_t launch_finalize(int batch, int ntiles, int nslots, const double* partials, long long slot_stride,
                            double scale, int phase, double* resp, long long resp_stride,
                            long long resp_offset, int* flag, hipStream_t s);
 hipError_t launch_clear_flag(int* flag, hipStream_t s);

@@ -659,7 +659,7 @@ __global__ void __launch_bounds__((PlanOf<T, NS, NP, CPT_>::NT), 2) stage_kernel
     if (tid == 0) {
       double s = 0.0;
       for (int w = 0; w < NW; ++w) s += wsum[w];
-      a.partials[((long long)b * kRespSlots + a.slot) * a.npartials + tile] = s;
+      a.partials[(long long)b * a.npartials + tile] = s;
     }
   }
 }

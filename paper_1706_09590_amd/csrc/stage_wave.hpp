@@ -812,7 +812,7 @@ __global__ void __launch_bounds__(64 * WPB, OCC) stage_wave_kernel(StageArgs a) 
       }
 #pragma unroll
       for (int off = L / 2; off > 0; off >>= 1) tr += __shfl_xor(tr, off, 64);
-      if (lig == 0 && q < nq) a.partials[((long long)b * kRespSlots + a.slot) * a.npartials + q] = tr;
+      if (lig == 0 && q < nq) a.partials[(long long)b * a.npartials + q] = tr;
     }
   }
 }
