@@ -43,9 +43,10 @@ struct Layout {
   size_t elem = 0;
   long long member_elems = 0, level_elems = 0, comp_elems = 0;
   size_t state_bytes = 0;
-  size_t off_y = 0, off_va = 0, off_vb = 0, off_partials = 0, off_red = 0, off_tw = 0, off_flag = 0, off_mlev = 0;
+  size_t off_y = 0, off_va = 0, off_vb = 0, off_partials = 0, off_red = 0, off_tw = 0, off_wtw = 0, off_flag = 0, off_mlev = 0;
   size_t off_dtab = 0, off_gtab = 0, off_ctab = 0, off_mtab = 0, off_bath = 0, off_psym = 0;
-  int n1 = 0, n2 = 0;
+  int n1 = 0, n2 = 0;    // FFT plan of the workgroup variant
+  int wn1 = 0, wn2 = 0;  // of the wave variant (0: none)
   size_t total = 0;
   size_t red_count = 0;
   int slots = 0;      // response samples buffered between finalisations
@@ -133,6 +134,16 @@ Layout make_layout(const qhfpe_params* p) {
   L.n2 = pl->n2;
   L.off_tw = off;
   off += align_up((size_t)pl->n1 * (pl->n2 + 1) * 2 * L.elem);
+  // the wave variant's twiddle factors, where its plan is another
+  L.off_wtw = L.off_tw;
+  if (wave_ok) {
+    L.wn1 = wave_n1(p->np);
+    L.wn2 = p->np / L.wn1;
+    if (L.wn1 != L.n1) {
+      L.off_wtw = off;
+      off += align_up((size_t)L.wn1 * (L.wn2 + 1) * 2 * L.elem);
+    }
+  }
   const int ns = p->n_states;
   L.off_dtab = off;
   off += align_up((size_t)ns * L.comp_elems * L.elem);
@@ -463,7 +474,7 @@ struct qhfpe_handle {
   void* vb() const { return ws + L.off_vb; }
   double* partials() const { return reinterpret_cast<double*>(ws + L.off_partials); }
   double* red() const { return reinterpret_cast<double*>(ws + L.off_red); }
-  void* twiddle() const { return ws + L.off_tw; }
+  void* twiddle() const { return ws + (wave() ? L.off_wtw : L.off_tw); }
   void* dtab() const { return ws + L.off_dtab; }
   void* gtab() const { return ws + L.off_gtab; }
   void* ctab() const { return ws + L.off_ctab; }
@@ -666,7 +677,7 @@ int install_surfaces(qhfpe_t* h, const Surfaces& U) {
   double coup[QHFPE_MAX_STATES][QHFPE_MAX_STATES];
   if (!multiplier_tables(h->p, U, h->dq, h->dp, dt, gt, ct, &coup_const, coup))
     return fail(QHFPE_EINVAL, "the potential has a non-finite value on the grid");
-  if (wave_exists(h->p.np)) wave_tables(h->p, h->L.n1, h->L.n2, dt, gt, ct, mt);
+  if (wave_exists(h->p.np)) wave_tables(h->p, h->L.wn1, h->L.wn2, dt, gt, ct, mt);
   hipError_t e = hipSuccess;
   auto up = [&](void* dst, const std::vector<double>& src) {
     if (e != hipSuccess || src.empty()) return;
@@ -754,7 +765,10 @@ int qhfpe_create(const qhfpe_params* params, void* d_workspace, size_t bytes, vo
       if (e == hipSuccess) e = hipStreamSynchronize(h->stream);  // f is a temporary
     }
   };
-  up(h->twiddle(), tw);
+  up(h->ws + L.off_tw, tw);
+  std::vector<double> wtw;
+  if (L.off_wtw != L.off_tw) twiddle_table(params->np, L.wn1, L.wn2, wtw);
+  up(h->ws + L.off_wtw, wtw);
   up(h->psym(), sym);
   if (e == hipSuccess)
     e = hipMemcpyAsync(h->bath(), bath.data(), bath.size() * sizeof(double), hipMemcpyHostToDevice, h->stream);

@@ -26,13 +26,19 @@ struct Plan {
 };
 constexpr Plan kPlans[] = {
     {8, 4, 2},   {12, 4, 3},  {16, 4, 4},   {24, 6, 4},    {32, 8, 4},    {48, 8, 6},
-    {64, 8, 8},  {96, 8, 12}, {128, 16, 8}, {192, 16, 12}, {256, 16, 16},
+    {64, 8, 8},  {96, 12, 8}, {128, 16, 8}, {192, 16, 12}, {256, 16, 16},
 };
 inline const Plan* find_plan(int np) {
   for (const Plan& p : kPlans)
     if (p.np == np) return &p;
   return nullptr;
 }
+// The wave variant's plan: the same but at np = 96, where its first pass takes 8
+// points (a wave's 64 lanes hold whole transforms of the second pass, which
+// has np / 8 = 12 of them) and the workgroup variant's 12 (three states with
+// q-dependent couplings, 96 x 96 x 5, 16 members: FP32 38.1 us a stage against 41.1
+// with 8, FP64 80.7 against 86.4; two states, code 2: 14.0 / 15.5, 21.9 / 23.2).
+constexpr int wave_n1(int np) { return np == 96 ? 8 : np <= 24 ? 0 : np <= 64 ? 8 : 16; }
 
 // Stage workgroup shape: G = max(1, 256/np) groups of np threads; each
 // thread owns one p node of CPT consecutive q columns; a tile is TQ = G*CPT
@@ -157,7 +163,7 @@ struct StageArgs {
   const void* y;         // RK4 base state (nullptr: treated as zero)
   void* out;             // y + coef * L v
   double* partials;      // [B][npartials] level-0 trace partials of one sample, or nullptr
-  const void* twiddle2;  // [n1][n2+1] complex exp(+2 pi i (n2 k1 mod np)/np), state precision
+  const void* twiddle2;  // [n1][n2+1] complex exp(+2 pi i (n2 k1 mod np)/np), state precision, of the variant's plan
   const void* dtab;      // [ns][nq][np]: (U_j(q+r/2) - U_j(q-r/2)) / (2 hbar np), 0 at Nyquist
   const void* gtab;      // [npair][nq][np]: (U_j(q+r/2) - U_k(q-r/2)) / (hbar np), j < k
   const void* ctab;      // [npair][2][nq][np]: U_jl(q + r/2), U_jl(q - r/2) / (hbar np), pair j < l

@@ -44,7 +44,7 @@ QHFPE_SPLIT(24, 6, 4)
 QHFPE_SPLIT(32, 8, 4)
 QHFPE_SPLIT(48, 8, 6)
 QHFPE_SPLIT(64, 8, 8)
-QHFPE_SPLIT(96, 8, 12)
+QHFPE_SPLIT(96, 12, 8)
 QHFPE_SPLIT(128, 16, 8)
 QHFPE_SPLIT(192, 16, 12)
 QHFPE_SPLIT(256, 16, 16)

@@ -54,7 +54,7 @@ namespace qhfpe {
 template <int NS_, int NP_, int C_, int WPB_>
 struct WavePlan {
   static constexpr int NS = NS_, NP = NP_, C = C_;
-  static constexpr int N1 = FftSplit<NP>::N1, N2 = FftSplit<NP>::N2;
+  static constexpr int N1 = wave_n1(NP), N2 = NP / N1;
   static constexpr int K = wave_nodes(NP);     // p nodes per lane
   static constexpr int L = NP / K;             // lanes per column
   static constexpr int G = 64 / L;             // lane groups
@@ -93,7 +93,7 @@ struct WavePlan {
   }
   // W22 does not share its transform with another component of its column
   __host__ __device__ static constexpr bool alone(int comp) { return NS == 3 && comp == 2; }
-  static_assert(K * L == NP && (L == 16 || L == 32 || L == 64) && 64 % N1 == 0 && N2 % 2 == 0, "wave plan");
+  static_assert(K * L == NP && (L == 16 || L == 32 || L == 64) && 64 % N1 == 0 && N1 * N2 == NP && N2 % 2 == 0, "wave plan");
 };
 
 // complex values in LDS: one 8- or 16-byte access each

@@ -5,6 +5,8 @@ bits on either side of each rule's line."""
 import numpy as np
 import pytest
 
+from helpers import oracle_model
+from oracle import qhfpe_oracle as O
 from paper_1706_09590_amd import inputs
 
 torch = pytest.importorskip("torch")
@@ -58,3 +60,23 @@ def test_samples_do_not_depend_on_the_batch(ns, np_, nq, depth, batch, tile):
     for m in (0, batch // 2, batch - 1):
         one, _ = run(d, batch, "fp32", tile, steps=steps, member=m)
         assert np.array_equal(one[0], tr[m]), m
+
+
+@pytest.mark.parametrize("ns,tile,precision,q_dependent", [
+    (2, 2, "fp64", False), (2, 2, "fp32", False), (2, 8, "fp32", False), (2, 0, "fp64", False), (2, 0, "fp32", False),
+    (3, 4, "fp32", False), (3, 0, "fp64", False), (3, 2, "fp64", True), (3, 2, "fp32", True)])
+def test_every_variant_at_96_points(ns, tile, precision, q_dependent):
+    """The variants split 96 points differently (their own twiddle factors and
+    multiplier order): each against the oracle, bars as in test_gpu_parity.py."""
+    d = model(ns, 96, 13, 2, q_dependent)
+    W = inputs.random_hierarchy(2, ns, 13, 96, seed=960 + ns + tile, smooth=False)
+    P = qhfpe.Propagator(d, batch=1, precision=precision)
+    try:
+        P.set_tile(tile)
+        P.set_state(torch.from_numpy(W[None]))
+        P.apply_rhs()
+        got = P.get_state().cpu().numpy()[0]
+    finally:
+        P.close()
+    ref = O.rhs(oracle_model(d), W)
+    assert np.linalg.norm(got - ref) <= (1e-12 if precision == "fp64" else 1e-5) * np.linalg.norm(ref)
