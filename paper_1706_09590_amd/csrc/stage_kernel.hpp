@@ -147,7 +147,11 @@ __device__ __forceinline__ cx<T> coupling_rspace(const cx<T> (&H)[NS][NS], const
 // members have depths of their own (StageArgs::mlev): member b owns
 // ntiles * (its levels) consecutive units, and every row of ntiles units
 // belongs to one member.  (A compile-time switch: the lookup's dependent
-// scalar loads would otherwise lengthen every wave's start.)
+// scalar loads would otherwise lengthen every wave's start.)  EXACT: the
+// divisions by products with the launch's constants, for the wave variant; a
+// small launch of this one waits for those constants longer than it takes to
+// divide (us per stage, division / product: two states, code 2, 32 x 32 x 5 FP64
+// 8.10 / 8.26, default 24 x 24 x 5 FP32 9.09 / 9.20).
 struct UnitPos {
   int b, tile, n, depth;
 };
@@ -156,19 +160,19 @@ __device__ __forceinline__ int stage_units(const StageArgs& a) {
   if constexpr (MIX) return a.ntiles * (a.mlev[a.mfirst + a.batch] - a.mlev[a.mfirst]);
   return a.ntiles * (a.depth + 1) * a.batch;
 }
-template <bool MIX>
+template <bool MIX, bool EXACT>
 __device__ __forceinline__ UnitPos unit_pos(const StageArgs& a, int t) {
   UnitPos u;
   if constexpr (!MIX) {
-    const int row = a.by_levels.div(t);
+    const int row = EXACT ? a.by_levels.div(t) : t / (a.depth + 1);
     u.n = t - row * (a.depth + 1);
-    u.b = a.by_tiles.div(row);
+    u.b = EXACT ? a.by_tiles.div(row) : row / a.ntiles;
     u.tile = row - u.b * a.ntiles;
     u.depth = a.depth;
     return u;
   }
   const int tg = t + a.ntiles * a.mlev[a.mfirst];
-  const int bg = a.lev_member[a.by_tiles.div(tg)];
+  const int bg = a.lev_member[EXACT ? a.by_tiles.div(tg) : tg / a.ntiles];
   const int r0 = a.mlev[bg], L = a.mlev[bg + 1] - r0;
   const int local = tg - a.ntiles * r0;
   u.n = local % L;
@@ -208,7 +212,7 @@ __global__ void __launch_bounds__((PlanOf<T, NS, NP, CPT_>::NT), 2) stage_kernel
   // levels run fastest: the blocks of every level of one q tile are
   // resident together, so the reads of v^(n) by levels n - 1 and n + 1
   // hit the copy that level n's own block brought into L2
-  const UnitPos pos = unit_pos<MIX>(a, lb);
+  const UnitPos pos = unit_pos<MIX, false>(a, lb);
   const int n = pos.n, tile = pos.tile, b = pos.b;
   const int q0 = tile * TQ;
   const int nq = a.nq;

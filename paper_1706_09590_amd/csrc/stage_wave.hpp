@@ -211,7 +211,7 @@ __global__ void __launch_bounds__(64 * WPB, OCC) stage_wave_kernel(StageArgs a) 
   const bool active = task_id < ntasks;
   if (WPB == 1 && !active) return;
   const int task = active ? task_id : 0;
-  const UnitPos pos = unit_pos<MIX>(a, task);
+  const UnitPos pos = unit_pos<MIX, true>(a, task);
   const int n = pos.n, tile = pos.tile, b = pos.b;
   const int grp = L == 64 ? 0 : lane / L, lig = L == 64 ? lane : lane % L;
   const int c0l = C * grp;            // this lane's first task column
