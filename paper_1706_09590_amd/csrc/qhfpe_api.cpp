@@ -399,11 +399,19 @@ struct qhfpe_handle {
   // members, 0.6 MB of state, 4.9 / 6.3; 128x128x7 FP32 three, 5.5 MB, 8.6 / 9.4;
   // 96x96x7 FP64 three, 6.2 MB, 8.3 / 8.8; 128x128x7 FP32 four, 7.3 MB, 9.35 /
   // 9.3; 96x96x7 FP32 eight, 8.3 MB, 10.1 / 8.6; 256x256x9 FP64 two, 75 MB, 30 /
-  // 21.9).  A recorded step is not enqueued launch by launch and keeps the groups.
+  // 21.9).  The workgroup variant fills the CUs with fewer units; past one round
+  // of them two groups are over sooner, three never are (one / two groups, MB of
+  // state below 7: code 2 FP64 256 units 64x64 8.2 / 10.1, 272 128x68 10.7 / 9.9, 384
+  // 32x32 10.6 / 9.7, 96x96 9.8 / 10.2, 400 256x99 13.3 / 12.2, 48x48 10.6 / 9.9;
+  // three states FP32 256 units 16.6 / 17.1, 352 18.2 / 16.7; two states FP32 768 units
+  // 128x128 9.7 / 10.3, 880 48x48 11.7 / 10.6; three groups FP64 276 units 12.8 / 13.9).
+  // A recorded step is not enqueued launch by launch and keeps the groups.
   int step_groups(bool recorded) const {
     constexpr double kLaunchBoundBytes = 7.0e6;
     const bool small = (double)all_levels() * L.level_elems * L.elem < kLaunchBoundBytes;
-    return groups_req == 0 && small && !recorded ? 1 : groups();
+    if (groups_req != 0 || !small || recorded) return groups();
+    const int round = 256 * (ns == 2 && p.precision != QHFPE_FP64 ? 3 : 1);
+    return wave() || groups() != 2 || units(0, p.batch) <= round ? 1 : groups();
   }
 
   hipError_t make_groups(int n) {

@@ -49,6 +49,17 @@ def run(d, batch, precision, tile=0, groups=0, steps=(4, 2), member=None):
         P.close()
 
 
+@pytest.mark.parametrize("ns,np_,nq,tile,q_dependent,batch", [
+    (2, 48, 48, 2, False, 10), (2, 48, 48, 2, False, 11), (2, 24, 24, 0, False, 16), (2, 128, 64, 4, False, 3),
+    (3, 64, 30, 2, True, 16), (3, 96, 24, 2, True, 8), (3, 96, 24, 2, True, 9)])
+def test_workgroup_variant_agrees_with_any_grouping(ns, np_, nq, tile, q_dependent, batch):
+    d = model(ns, np_, nq, 4, q_dependent)
+    want = run(d, batch, "fp64", tile, 1)
+    for groups in (0, 2, 3):
+        got = run(d, batch, "fp64", tile, groups)
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), groups
+
+
 @pytest.mark.parametrize("ns,np_,nq,depth,batch,tile", [(2, 32, 8, 0, 1300, 0), (2, 32, 8, 0, 1300, 2), (2, 128, 64, 0, 40, 0),
                                                         (3, 96, 21, 0, 260, 0), (2, 24, 9, 0, 700, 0)])
 def test_samples_do_not_depend_on_the_batch(ns, np_, nq, depth, batch, tile):
