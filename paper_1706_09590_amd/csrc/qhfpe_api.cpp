@@ -393,6 +393,9 @@ struct qhfpe_handle {
     return std::min(want, p.batch);
   }
 
+  // first member of group g of G
+  int group_first(int g, int G) const { return (int)((long long)g * p.batch / G); }
+
   // Groups of one step call.  The default rule's groups overlap launches, but each
   // costs the host 3.2 us per stage to enqueue, so where one launch of all members
   // is over sooner it is one (us per stage, one / two groups: 48x48x4 FP32 four
@@ -461,7 +464,13 @@ struct qhfpe_handle {
   // one shape for all of the handle's launches, whatever their member groups
   WaveShape shape() const {
     const long long columns = (p.nq + wave_groups(p.np) - 1) / wave_groups(p.np);
-    return wave_shape((int)L.elem, ns, p.np, qcoup != 0, all_levels() * columns, stream_out());
+    const int G = groups();
+    long long largest = 0;
+    for (int g = 0; g < G; ++g) {
+      const int b0 = group_first(g, G), b1 = group_first(g + 1, G);
+      largest = std::max<long long>(largest, mixed ? hmlev[b1] - hmlev[b0] : (long long)levels * (b1 - b0));
+    }
+    return wave_shape((int)L.elem, ns, p.np, qcoup != 0, all_levels() * columns, G * largest * columns, G > 1, stream_out());
   }
   // q columns per unit of a stage launch
   int tq() const { return wave() ? wave_columns_of(p.np, shape().c) : plan_groups(p.np) * cpt; }
@@ -1077,7 +1086,7 @@ int step_enqueue(qhfpe_t* h, int64_t nsteps, int32_t stride, double* d_resp) {
   // (a later recording may want them)
   if (nsteps > 0 && !recorded && h->groups() > 1) HIP_TRY(h->make_groups(h->groups()));
   int first[kMaxGroups + 1];
-  for (int g = 0; g <= G; ++g) first[g] = (int)((long long)g * h->p.batch / G);
+  for (int g = 0; g <= G; ++g) first[g] = h->group_first(g, G);
   hipStream_t gs[kMaxGroups];
   StageArgs g1[kMaxGroups], g2[kMaxGroups], g3[kMaxGroups];
   if (G > 1) {

@@ -87,7 +87,8 @@ constexpr int wave_groups(int np) { return 64 * wave_nodes(np) / np; }  // lane 
 inline int wave_columns_of(int np, int c) { return wave_groups(np) * c; }
 
 // The shape for a handle whose stages would be `waves` waves with one column
-// per lane group.  Results do not depend on it.  One column per wave keeps a
+// per lane group; launched in member groups, `spread` is the count of groups
+// times the largest one's waves (else `waves`).  Results do not depend on it.  One column per wave keeps a
 // wave's chain short (few loads to wait for, one item per FFT round) but loads
 // 7 window columns per column and leaves FFT lanes idle: it wins while the
 // waves find SIMDs of their own.  More columns per wave save loads and fill
@@ -98,10 +99,15 @@ inline int wave_columns_of(int np, int c) { return wave_groups(np) * c; }
 //   waves 6.2 / 6.5 / 8.1, 10240 waves 14.3 / 10.9 / 10.2; 256 FP64, 192 waves
 //   9.0 / 10.1, 2304 waves 21.2 / 18.2; 96 FP64 (two lane groups), 1344 waves
 //   10.3 / 11.4, 5376 waves 23.5 / 19.8 / 32.7.
-//   three states: 128 FP32, 7544 waves 33.8 / 34.2, 13530 waves 49.2 / 46.9;
-//   128 FP64, 8036 waves 48.5 / 53.3, 12300 waves 86.5 / 86.2; 64 FP64, 11520
-//   waves 41.8 / 36.6; 256 FP32, 9216 waves 55.6 with one (two would leave LDS
-//   for six waves a CU).
+//   128 FP32, two / four columns: one launch 10000 waves 16.7 / 16.4, 10500 18.1 /
+//   16.5; two groups of 8 members each 10000 14.4 / 15.4, 11000 15.8 / 15.6; five
+//   members (three and two) 8500 waves 13.1 / 14.6, 9000 15.2 / 14.6.
+//   three states: 128 FP32, one launch 7700 waves 32.1 / 32.8, 8400 34.9 / 34.6, 9600
+//   39.7 / 35.9; in groups, whose launches overlap, sooner: 16 members 4400 waves
+//   17.8 / 18.1, 5000 19.4 / 18.7, 9600 35.2 / 30.4; 128 FP64, one launch 10500 75.6 /
+//   77.8, 11500 87.4 / 85.0, in groups five members 3800 24.3 / 24.5, 4400 29.4 / 27.0;
+//   64 FP64, 11520 waves 41.8 / 36.6; 256 FP32, 9216 waves 55.6 with one (two would
+//   leave LDS for six waves a CU).
 // Components in flight: with SIMDs to spare a one-column wave issues two (three
 // for nine components; in FP32 all four of two states: 64 x 64 5.2 against
 // 5.3 us); otherwise the staggered schedule, except FP32 at 256, whose second
@@ -109,11 +115,13 @@ inline int wave_columns_of(int np, int c) { return wave_groups(np) * c; }
 // Workgroups: two waves spread more evenly over the CUs, four share the tables
 // (256 FP64 1152 tasks 18.2 against 21.4 us, 9216 tasks 111 against 105 us;
 // at 192 four win throughout).
-inline WaveShape wave_shape(int elem_bytes, int ns, int np, bool qcoup, long long waves, bool stream) {
+inline WaveShape wave_shape(int elem_bytes, int ns, int np, bool qcoup, long long waves, long long spread, bool grouped,
+                            bool stream) {
   const bool f32 = elem_bytes == 4;
   if (ns == 3) {
     const bool pairs = np == 128 || np == 64;  // two columns fit
-    if (pairs && (stream || waves >= (np == 64 ? 7000 : 11000))) return {2, kStaggered, 2};
+    const long long two = np == 64 ? 7000 : grouped ? 4700 : f32 ? 8400 : 11000;
+    if (pairs && (stream || (np == 64 ? waves : spread) >= two)) return {2, kStaggered, 2};
     if ((f32 || pairs) && !stream && waves <= 2000) return {1, 3, 1};
     return {1, kStaggered, 2};
   }
@@ -126,7 +134,8 @@ inline WaveShape wave_shape(int elem_bytes, int ns, int np, bool qcoup, long lon
     return {2, pf, stream || waves > 7000 ? 4 : 2};
   }
   if (np == 192) return {2, kStaggered, 4};
-  if ((np == 128 && (stream || waves >= 13000)) || (np == 64 && (stream || waves >= 7000))) return {4, kStaggered, 4};
+  if (np == 128 && (stream || waves >= 13000 || (f32 && !qcoup && spread >= 10300))) return {4, kStaggered, 4};
+  if (np == 64 && (stream || waves >= 7000)) return {4, kStaggered, 4};
   return {2, kStaggered, 2};
 }
 

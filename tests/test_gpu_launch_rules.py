@@ -60,6 +60,21 @@ def test_workgroup_variant_agrees_with_any_grouping(ns, np_, nq, tile, q_depende
         assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), groups
 
 
+@pytest.mark.parametrize("ns,precision,waves", [
+    (2, "fp32", 9400), (2, "fp32", 10700), (3, "fp32", 4500), (3, "fp32", 5000), (3, "fp32", 8800), (3, "fp64", 4900),
+    (3, "fp64", 11400)])
+def test_columns_per_wave_at_128_points(ns, precision, waves):
+    """Five members (uneven groups): every grouping and a member alone."""
+    d = model(ns, 128, waves // 20, 3)
+    want = run(d, 5, precision, groups=1)
+    for groups in (2, 3, 4):
+        got = run(d, 5, precision, groups=groups)
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), groups
+    for m in (0, 4):
+        tr, st = run(d, 5, precision, member=m)
+        assert np.array_equal(tr[0], want[0][m]) and np.array_equal(st[0], want[1][m]), m
+
+
 @pytest.mark.parametrize("ns,np_,nq,depth,batch,tile", [(2, 32, 8, 0, 1300, 0), (2, 32, 8, 0, 1300, 2), (2, 128, 64, 0, 40, 0),
                                                         (3, 96, 21, 0, 260, 0), (2, 24, 9, 0, 700, 0)])
 def test_samples_do_not_depend_on_the_batch(ns, np_, nq, depth, batch, tile):
