@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -149,10 +150,10 @@ Layout make_layout(const qhfpe_params* p) {
   off += align_up((size_t)ns * L.comp_elems * L.elem);
   L.off_gtab = off;
   off += align_up((size_t)(ns * (ns - 1) / 2) * L.comp_elems * L.elem);
-  L.off_ctab = off;
-  off += align_up((size_t)(ns * (ns - 1)) * L.comp_elems * L.elem);
   L.off_mtab = off;
   if (wave_ok) off += align_up((size_t)wave_table_planes(ns) * L.comp_elems * L.elem);
+  L.off_ctab = off;
+  if (workgroup_qc(ns, p->np)) off += align_up((size_t)(ns * (ns - 1)) * L.comp_elems * L.elem);
   L.off_bath = off;
   off += align_up((size_t)p->batch * kBathStride * sizeof(double));
   L.off_psym = off;
@@ -204,63 +205,104 @@ struct Surfaces {
   }
 };
 
-// r-space multipliers at (q_i, r_m) for every table the kernels use:
+// r-space multipliers at (q_i, r_m) for the tables the kernels use, each computed
+// in FP64 and rounded once to the state precision:
 //   dtab[j] = (U_jj(q + r/2) - U_jj(q - r/2)) / (2 hbar np)
 //   gtab[pair j<k] = (U_jj(q + r/2) - U_kk(q - r/2)) / (hbar np)
+//   mtab: the wave variant's planes (nullptr: it does not exist at this np), each
+//     q row permuted so that the n2 values m = k1 + n1 k2 (k2 = 0..n2-1) of row
+//     k1 are contiguous.  The packed diagonals (0, 1) of a column need the sum
+//     and the difference of their tables.  Two states: dtab 0 + dtab 1,
+//     dtab 0 - dtab 1, the coherence table; three states: the same sum and
+//     difference, dtab 2, the coherence tables of the pairs (0,1), (0,2), (1,2).
+// and, written for a q-dependent coupling only,
 //   ctab[2 pair], ctab[2 pair + 1] = U_jk(q + r/2) / (hbar np), U_jk(q - r/2) / (hbar np)
+//     (the workgroup variant's; nullptr: it has none), and the same of two states
+//     as planes 3 and 4 of mtab.
 // Arguments are clamped to the q grid; at the Nyquist column both arguments
 // take the average of the two values.  Returns false if a value is not
 // finite; *coup_const tells whether every off-diagonal U_jl had one value
 // (then coup[j][l] holds it divided by hbar).
-bool multiplier_tables(const qhfpe_params& p, const Surfaces& U, double dq, double dp, std::vector<double>& dtab,
-                       std::vector<double>& gtab, std::vector<double>& ctab, bool* coup_const,
-                       double coup[QHFPE_MAX_STATES][QHFPE_MAX_STATES]) {
-  const int ns = p.n_states, nq = p.nq, np = p.np;
+// Row by row, so that the values of a row stay in the first-level cache and its
+// quotients are taken two at a time.
+template <typename T>
+bool multiplier_tables(const qhfpe_params& p, const Surfaces& U, double dq, double dp, const std::vector<int>& wave_at,
+                       T* dtab, T* gtab, T* mtab, T* ctab, bool* coup_const, double coup[QHFPE_MAX_STATES][QHFPE_MAX_STATES]) {
+  constexpr int S = QHFPE_MAX_STATES, kMaxNp = 256;
+  const int ns = p.n_states, nq = p.nq, np = p.np, npairs = ns * (ns - 1) / 2;
   const double dr = 2.0 * M_PI * p.hbar / (np * dp);
   const double qlo = p.q_min, qhi = p.q_min + (nq - 1) * dq;
   auto clampq = [&](double x) { return x < qlo ? qlo : (x > qhi ? qhi : x); };
   const size_t plane = (size_t)nq * np;
-  dtab.assign((size_t)ns * plane, 0.0);
-  gtab.assign((size_t)(ns * (ns - 1) / 2) * plane, 0.0);
-  ctab.assign((size_t)(ns * (ns - 1)) * plane, 0.0);
-  double first[QHFPE_MAX_STATES][QHFPE_MAX_STATES] = {};
+  const double dscale = 2.0 * p.hbar * np, scale = p.hbar * np;
+  double up[S][S][kMaxNp], um[S][S][kMaxNp];          // U_jl(q + r/2), U_jl(q - r/2) of the row, j <= l
+  double d[S][kMaxNp], g[3][kMaxNp], c[2][kMaxNp];    // its quotients
+  double first[S][S] = {};
   bool seen = false, same = true, finite = true;
+  // the quotients of the coupling of pair pr in row i
+  auto coupling_row = [&](int i, int pr, const double* vp, const double* vm) {
+    for (int m = 0; m < np; ++m) c[0][m] = vp[m] / scale;
+    for (int m = 0; m < np; ++m) c[1][m] = vm[m] / scale;
+    for (int t = 0; t < 2; ++t) {
+      if (ctab) std::copy_n(c[t], np, ctab + (2 * pr + t) * plane + (size_t)i * np);
+      if (mtab && ns == 2)
+        for (int m = 0; m < np; ++m) mtab[(3 + t) * plane + (size_t)i * np + wave_at[m]] = T(c[t][m]);
+    }
+  };
   for (int i = 0; i < nq; ++i) {
     const double q = p.q_min + i * dq;
+    const bool was_same = same;
     for (int m = 0; m < np; ++m) {
       const int mh = (m <= np / 2) ? m : m - np;
       const double xp = clampq(q + 0.5 * mh * dr), xm = clampq(q - 0.5 * mh * dr);
-      const bool nyq = (m == np / 2);
-      double up[QHFPE_MAX_STATES][QHFPE_MAX_STATES], um[QHFPE_MAX_STATES][QHFPE_MAX_STATES];
       for (int j = 0; j < ns; ++j)
         for (int l = j; l < ns; ++l) {
           if (U.up_tab) {
             const size_t t = (((size_t)j * ns + l) * nq + i) * np + m;
-            up[j][l] = U.up_tab[t];
-            um[j][l] = U.um_tab[t];
+            up[j][l][m] = U.up_tab[t];
+            um[j][l][m] = U.um_tab[t];
           } else {
-            up[j][l] = U(j, l, xp);
-            um[j][l] = U(j, l, xm);
+            up[j][l][m] = U(j, l, xp);
+            um[j][l][m] = U(j, l, xm);
           }
-          finite = finite && std::isfinite(up[j][l]) && std::isfinite(um[j][l]);
-          if (nyq && !U.up_tab) up[j][l] = um[j][l] = 0.5 * (up[j][l] + um[j][l]);
-          if (l > j) {
-            if (!seen) first[j][l] = up[j][l];
-            same = same && up[j][l] == first[j][l] && um[j][l] == first[j][l];
-          }
+          finite = finite && std::isfinite(up[j][l][m]) && std::isfinite(um[j][l][m]);
         }
-      seen = true;
-      const size_t at = (size_t)i * np + m;
-      for (int j = 0; j < ns; ++j) dtab[j * plane + at] = (up[j][j] - um[j][j]) / (2.0 * p.hbar * np);
-      int pr = 0;
-      for (int j = 0; j < ns; ++j)
-        for (int k = j + 1; k < ns; ++k, ++pr) gtab[pr * plane + at] = (up[j][j] - um[k][k]) / (p.hbar * np);
-      pr = 0;
-      for (int j = 0; j < ns; ++j)
-        for (int k = j + 1; k < ns; ++k, ++pr) {
-          ctab[2 * pr * plane + at] = up[j][k] / (p.hbar * np);
-          ctab[(2 * pr + 1) * plane + at] = um[j][k] / (p.hbar * np);
+    }
+    for (int j = 0; j < ns; ++j)
+      for (int l = j; l < ns; ++l) {
+        double &a = up[j][l][np / 2], &b = um[j][l][np / 2];
+        if (!U.up_tab) a = b = 0.5 * (a + b);
+        if (l == j) continue;
+        if (!seen) first[j][l] = up[j][l][0];
+        for (int m = 0; m < np; ++m) same = same && up[j][l][m] == first[j][l] && um[j][l][m] == first[j][l];
+      }
+    seen = true;
+    for (int j = 0; j < ns; ++j) {
+      for (int m = 0; m < np; ++m) d[j][m] = (up[j][j][m] - um[j][j][m]) / dscale;
+      std::copy_n(d[j], np, dtab + j * plane + (size_t)i * np);
+    }
+    for (int pr = 0, j = 0; j < ns; ++j)
+      for (int k = j + 1; k < ns; ++k, ++pr) {
+        for (int m = 0; m < np; ++m) g[pr][m] = (up[j][j][m] - um[k][k][m]) / scale;
+        std::copy_n(g[pr], np, gtab + pr * plane + (size_t)i * np);
+        if (same) continue;
+        // (at the first row with another value the rows before it held the constants)
+        if (was_same) {
+          double held[kMaxNp];
+          std::fill_n(held, np, first[j][k]);
+          for (int r = 0; r < i; ++r) coupling_row(r, pr, held, held);
         }
+        coupling_row(i, pr, up[j][k], um[j][k]);
+      }
+    if (mtab) {
+      T* const w = mtab + (size_t)i * np;
+      for (int m = 0; m < np; ++m) {
+        const int at = wave_at[m];
+        w[at] = T(d[0][m] + d[1][m]);
+        w[plane + at] = T(d[0][m] - d[1][m]);
+        if (ns == 3) w[2 * plane + at] = T(d[2][m]);
+        for (int pr = 0; pr < npairs; ++pr) w[(ns + pr) * plane + at] = T(g[pr][m]);
+      }
     }
   }
   *coup_const = same;
@@ -268,37 +310,6 @@ bool multiplier_tables(const qhfpe_params& p, const Surfaces& U, double dq, doub
     for (int l = 0; l < ns; ++l)
       coup[j][l] = (j == l || !same) ? 0.0 : first[std::min(j, l)][std::max(j, l)] / p.hbar;
   return finite;
-}
-
-// The multiplier tables of the wave variant in one array, each q row
-// permuted so that the n2 values m = k1 + n1 k2 (k2 = 0..n2-1) of row k1
-// are contiguous.  The packed diagonals (0, 1) of a column need the sum and
-// the difference of their tables.  Two states: dtab 0 + dtab 1, dtab 0 - dtab 1,
-// the coherence table, U_01(q + r/2) and U_01(q - r/2) (used only for a
-// q-dependent coupling).  Three states: the same sum and difference, dtab 2,
-// then the coherence tables of the pairs (0,1), (0,2), (1,2).
-void wave_tables(const qhfpe_params& p, int n1, int n2, const std::vector<double>& dtab,
-                 const std::vector<double>& gtab, const std::vector<double>& ctab, std::vector<double>& mtab) {
-  const int nq = p.nq, np = p.np, ns = p.n_states;
-  const int planes = wave_table_planes(ns);
-  const size_t plane = (size_t)nq * np;
-  mtab.assign(planes * plane, 0.0);
-  for (int t = 0; t < planes; ++t)
-    for (int i = 0; i < nq; ++i)
-      for (int k1 = 0; k1 < n1; ++k1)
-        for (int k2 = 0; k2 < n2; ++k2) {
-          const size_t src = (size_t)i * np + k1 + n1 * k2;
-          double v;
-          if (t == 0)
-            v = dtab[src] + dtab[plane + src];
-          else if (t == 1)
-            v = dtab[src] - dtab[plane + src];
-          else if (ns == 3)
-            v = t == 2 ? dtab[2 * plane + src] : gtab[(t - 3) * plane + src];
-          else
-            v = t == 2 ? gtab[src] : ctab[(t - 3) * plane + src];
-          mtab[t * plane + (size_t)i * np + (size_t)k1 * n2 + k2] = v;
-        }
 }
 
 // Symbols of the periodic fourth-order p-stencils in the DFT convention
@@ -531,7 +542,7 @@ struct qhfpe_handle {
     a.twiddle2 = twiddle();
     a.dtab = dtab();
     a.gtab = gtab();
-    a.ctab = ctab();
+    a.ctab = workgroup_qc(ns, p.np) ? ctab() : nullptr;
     a.mtab = wave_exists(p.np) ? mtab() : nullptr;
     a.qcoup = qcoup;
     a.bath = bath();
@@ -684,33 +695,50 @@ int norms(qhfpe_t* h, const void* buf, std::vector<double>& out) {
   return QHFPE_OK;
 }
 
-// Multiplier tables from the surfaces U, uploaded to the handle (computed in
-// FP64 and rounded once to the state precision).  When the surfaces are
-// rejected the handle's tables and coupling mode are unchanged; after a
-// failed upload (QHFPE_EHIP) the tables may be partly replaced.
+// Multiplier tables from the surfaces U, uploaded to the handle: those that some
+// variant reads, in one copy (two where a q-dependent coupling's table lies apart)
+// and one synchronisation.  When the surfaces are rejected the handle's tables
+// are unchanged; after a failed upload (QHFPE_EHIP) they may be partly replaced.
+template <typename T>
+int upload_surfaces(qhfpe_t* h, const Surfaces& U, bool* coup_const, double coup[QHFPE_MAX_STATES][QHFPE_MAX_STATES]) {
+  const Layout& L = h->L;
+  const size_t plane = (size_t)L.comp_elems;
+  const bool wave = wave_exists(h->p.np), wg = workgroup_qc(h->ns, h->p.np);
+  // the workspace's image from dtab to the end of ctab
+  const size_t n = (L.off_ctab - L.off_dtab) / sizeof(T) + (wg ? (size_t)(h->ns * (h->ns - 1)) * plane : 0);
+  std::unique_ptr<T[]> image(new (std::nothrow) T[n]);
+  if (!image) return fail(QHFPE_EINVAL, "out of host memory");
+  auto table = [&](size_t off) { return image.get() + (off - L.off_dtab) / sizeof(T); };
+  T* const mtab = wave ? table(L.off_mtab) : nullptr;
+  std::vector<int> wave_at(wave ? h->p.np : 0);
+  for (size_t m = 0; m < wave_at.size(); ++m) wave_at[m] = (int)(m % L.wn1 * L.wn2 + m / L.wn1);
+  if (!multiplier_tables(h->p, U, h->dq, h->dp, wave_at, table(L.off_dtab), table(L.off_gtab), mtab,
+                         wg ? table(L.off_ctab) : nullptr, coup_const, coup))
+    return fail(QHFPE_EINVAL, "the potential has a non-finite value on the grid");
+  const bool qc = !*coup_const;
+  hipError_t e = hipSuccess;
+  auto up = [&](size_t off, size_t count) {
+    if (e == hipSuccess) e = hipMemcpyAsync(h->ws + off, table(off), count * sizeof(T), hipMemcpyHostToDevice, h->stream);
+  };
+  // the padding between the tables travels along
+  auto pad = [&](size_t off, size_t count, size_t next) { std::fill(table(off) + count, table(next), T(0)); };
+  const size_t ng = (size_t)(h->ns * (h->ns - 1) / 2) * plane;
+  pad(L.off_dtab, h->ns * plane, L.off_gtab);
+  pad(L.off_gtab, ng, L.off_mtab);
+  const size_t planes = !wave || (qc && h->ns == 3) ? 0 : h->ns == 3 ? kWaveTables3 : qc ? kWaveTables : 3;
+  up(L.off_dtab, planes ? (L.off_mtab - L.off_dtab) / sizeof(T) + planes * plane : (L.off_gtab - L.off_dtab) / sizeof(T) + ng);
+  if (qc && wg) up(L.off_ctab, (size_t)(h->ns * (h->ns - 1)) * plane);
+  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);  // the image is a temporary
+  if (e != hipSuccess) return fail(QHFPE_EHIP, "uploading the potential tables: %s", hipGetErrorString(e));
+  return QHFPE_OK;
+}
+
 int install_surfaces(qhfpe_t* h, const Surfaces& U) {
-  std::vector<double> dt, gt, ct, mt;
   bool coup_const = true;
   double coup[QHFPE_MAX_STATES][QHFPE_MAX_STATES];
-  if (!multiplier_tables(h->p, U, h->dq, h->dp, dt, gt, ct, &coup_const, coup))
-    return fail(QHFPE_EINVAL, "the potential has a non-finite value on the grid");
-  if (wave_exists(h->p.np)) wave_tables(h->p, h->L.wn1, h->L.wn2, dt, gt, ct, mt);
-  hipError_t e = hipSuccess;
-  auto up = [&](void* dst, const std::vector<double>& src) {
-    if (e != hipSuccess || src.empty()) return;
-    if (h->p.precision == QHFPE_FP64) {
-      e = hipMemcpyAsync(dst, src.data(), src.size() * sizeof(double), hipMemcpyHostToDevice, h->stream);
-    } else {
-      std::vector<float> f = convert<float>(src);
-      e = hipMemcpyAsync(dst, f.data(), f.size() * sizeof(float), hipMemcpyHostToDevice, h->stream);
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);  // the host vectors are temporaries
-  };
-  up(h->dtab(), dt);
-  up(h->gtab(), gt);
-  up(h->ctab(), ct);
-  up(h->mtab(), mt);
-  if (e != hipSuccess) return fail(QHFPE_EHIP, "uploading the potential tables: %s", hipGetErrorString(e));
+  if (int rc = h->p.precision == QHFPE_FP64 ? upload_surfaces<double>(h, U, &coup_const, coup)
+                                            : upload_surfaces<float>(h, U, &coup_const, coup))
+    return rc;
   for (int j = 0; j < QHFPE_MAX_STATES; ++j)
     for (int l = 0; l < QHFPE_MAX_STATES; ++l) h->coup[j][l] = (j < h->ns && l < h->ns) ? coup[j][l] : 0.0;
   h->qcoup = coup_const ? 0 : 1;

@@ -77,6 +77,9 @@ constexpr bool wave_exists(int np) { return wave_nodes(np) != 0; }
 // public tile code 1
 inline bool wave_supported(int ns, int np) { return ns == 2 && (np == 128 || np == 256); }
 inline bool wave_variant_supported(int /*elem_bytes*/, int /*ns*/, int np) { return np == 128 || np == 256; }
+// the workgroup variant with a q-dependent coupling: not where the two-state wave
+// variant computes its tile code
+constexpr bool workgroup_qc(int ns, int np) { return ns == 3 || !wave_exists(np) || np == 128 || np == 256; }
 // Shape of a wave launch: q columns per lane group, components in flight (or
 // kStaggered), waves per workgroup.
 constexpr int kStaggered = 0;

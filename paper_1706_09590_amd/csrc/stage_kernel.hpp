@@ -690,7 +690,7 @@ template <typename T, int NS, int NP>
 hipError_t launch_stage_np(int cpt, const StageArgs& a, int nblocks, hipStream_t s) {
   constexpr bool kWave = wave_exists(NP) && NP != 128 && NP != 256;
   if (a.qcoup) {
-    if constexpr (!kWave || NS == 3)
+    if constexpr (workgroup_qc(NS, NP))
       if (cpt == kQcCpt) return launch_stage_variant<T, NS, NP, kQcCpt, true>(a, nblocks, s);
     return hipErrorInvalidValue;
   }

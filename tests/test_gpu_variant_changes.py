@@ -5,6 +5,8 @@ before, bit for bit."""
 import numpy as np
 import pytest
 
+from helpers import oracle_model
+from oracle import qhfpe_oracle as O
 from paper_1706_09590_amd import inputs
 
 torch = pytest.importorskip("torch")
@@ -99,3 +101,36 @@ def test_the_callers_variant_is_kept(np_):
     assert not same(want8, run(2, np_, "fp32", chosen(0)))  # (the variants differ by rounding)
     assert same(run(2, np_, "fp32", before), want8)
     assert same(run(2, np_, "fp32", under), want2)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("ns,np_,tile", [(2, 24, 0), (2, 64, 2), (2, 128, 1), (2, 128, 2), (3, 64, 2)])
+@pytest.mark.parametrize("kink", [-9.0, -0.5, 6.4])
+def test_couplings_that_differ_from_a_later_row_on(ns, np_, tile, kink, precision):
+    """Couplings of one value below a point, which lies under the grid, in its
+    middle or in the reach of its last columns only, against the oracle (one
+    operator application: FP64 1e-12, FP32 1e-5)."""
+    d = inputs.model_dict(inputs.SMALL_ABSORPTION["model"], n_states=ns, nq=18, np=np_, depth=1, dt=0.001)
+    if ns == 3:
+        d.update(poly=inputs.three_state_surfaces(0.3, 0.2), mu=[[0, 1, 0], [1, 0, 0.4], [0, 0.4, 0]])
+
+    def U(j, l, x):
+        if j == l:
+            return 0.5 * (x - 0.4 * j) ** 2 + 3.0 * j
+        return 0.2 + 0.1 * (j + l) + 0.3 * np.maximum(x - kink, 0.0) ** 2 / (1.0 + (x - kink) ** 2)
+
+    m = oracle_model(d)
+    m.potential_fn = lambda x: np.array([[U(j, l, np.asarray(x, dtype=np.float64)) for l in range(ns)] for j in range(ns)])
+    W = inputs.random_hierarchy(1, ns, 18, np_, seed=171 + np_)
+    P = qhfpe.Propagator(d, batch=1, precision=precision)
+    try:
+        P.set_potential(U)
+        if tile:
+            P.set_tile(tile)
+        P.set_state(torch.from_numpy(W[None]))
+        P.apply_rhs()
+        got = P.get_state().cpu().numpy()[0]
+    finally:
+        P.close()
+    ref = O.rhs(m, W)
+    assert np.linalg.norm(got - ref) <= (1e-12 if precision == "fp64" else 1e-5) * np.linalg.norm(ref)
