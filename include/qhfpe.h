@@ -229,14 +229,19 @@ int qhfpe_autotune(qhfpe_t* h, int32_t reps, int32_t* h_chosen);
  * grouping: every member is computed by the same kernels in the same order.
  * groups: 1 = one launch per stage for all members; 2..4 = that many ranges
  * (capped at the batch size); 0 = default (one group per member for batches
- * of up to 3 members, 2 groups for 4..16 members, else 1; a step that is not
- * recorded into a graph launches a state of less than 7 MB as one).  Only
- * qhfpe_step (and qhfpe_relax through it) uses the groups.
+ * of up to 3 members, 2 groups for 4..16 members, else 1).  With the default,
+ * a step that is not recorded into a graph launches a state of less than 7 MB
+ * as one: its groups would cost the host longer to enqueue than one launch
+ * takes (the workgroup variant keeps two groups past 256 workgroups, 768 for
+ * two states in FP32).  Only qhfpe_step (and qhfpe_relax through it) uses the
+ * groups.
  * QHFPE_EINVAL if groups is outside [0, 4]. */
 int qhfpe_set_streams(qhfpe_t* h, int32_t groups);
 
-/* Member groups qhfpe_step will use (after capping and the default rule; by
- * default a small state's steps take one). */
+/* The grouping of the handle: the groups asked for, or the default rule's,
+ * after capping.  Recorded steps and steps of larger states run in that many;
+ * what an unrecorded step of a small state takes by default is stated above
+ * and not told apart here. */
 int qhfpe_get_streams(const qhfpe_t* h, int32_t* groups);
 
 /* Initial state (Sec. III protocol; harmonic thermal Wigner function):

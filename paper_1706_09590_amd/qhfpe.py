@@ -288,6 +288,8 @@ class Propagator:
         _check(lib().qhfpe_set_streams(self.handle, int(groups)))
 
     def streams(self) -> int:
+        """The handle's grouping (qhfpe_get_streams): what recorded steps and
+        steps of states of 7 MB and more run in."""
         g = ctypes.c_int32(0)
         _check(lib().qhfpe_get_streams(self.handle, ctypes.byref(g)))
         return int(g.value)
