@@ -30,8 +30,8 @@
 // What bounds it: a small launch (each wave on a SIMD of its own) by one
 // wave's chain of launch, loads and FFT rounds, a large one by how well the
 // waves' load and transform phases overlap (no unit is saturated: 1024 members
-// of 128 x 128 x 7 levels in FP32 take 1.18 ms, of which VALU issue is 0.7 and
-// the bytes at the copy rate 0.85).  wave_shape (qhfpe_internal.hpp) holds the
+// of 128 x 128 x 7 levels in FP32 take 1.18 ms, of which VALU issue is 0.65, 1751
+// instructions a wave, and their 4.9 GB at the copy rate 0.89).  wave_shape (qhfpe_internal.hpp) holds the
 // rule and its measurements.  Against one fixed shape at 128 and 256 and the
 // workgroup variant elsewhere (us per stage, FP64): 48 x 48 x 4 levels, one
 // member 11.4 -> 5.5; 128 x 128 x 7 one member 10.9 -> 6.5; 96 x 96 x 7 four members
