@@ -365,8 +365,8 @@ int qhfpe_closure_gmfp_kernel(const qhfpe_t* h, float* h_kernel);
  * first two layers, the prior's central 5 x 5 taps in the third; taps of the
  * prior outside them are dropped), plus seeded weights of 1e-3 of that
  * scale; without one from the seeded weights alone.  d_state:
- * QHFPE_CLOSURE_TRAIN_FLOATS of device scratch (layers, gradients,
- * moments).  d_kernel receives the composite K (FP32,
+ * QHFPE_CLOSURE_TRAIN_FLOATS of device scratch (layers, moments,
+ * products and their gradients).  d_kernel receives the composite K (FP32,
  * QHFPE_CLOSURE_KERNEL_FLOATS), h_loss (may be NULL) its normalised data
  * loss sum (F(X) - Y)^2 / yy.  Runs on stream; synchronous. */
 int qhfpe_closure_train(const double* d_stats, const float* d_prior, double ridge, float* d_state, uint64_t seed,
