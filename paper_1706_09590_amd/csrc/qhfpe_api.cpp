@@ -472,7 +472,8 @@ struct qhfpe_handle {
     constexpr double kStreamBytes = 336.0 * 1024 * 1024;
     return 3.0 * (double)all_levels() * L.level_elems * L.elem > kStreamBytes;
   }
-  // one shape for all of the handle's launches, whatever their member groups
+  // one shape for all of the handle's launches, chosen by its size and grouping
+  // (a step's groups, a recorded step and an operator application have the same)
   WaveShape shape() const {
     const long long columns = (p.nq + wave_groups(p.np) - 1) / wave_groups(p.np);
     const int G = groups();
